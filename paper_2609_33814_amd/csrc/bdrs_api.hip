@@ -250,7 +250,6 @@ void build_side(const float* pts, const double* w, int count, int dim, const dou
   }
   hs.off.assign((size_t)sh.ntiles * dim * kTile, 0.f);
   TileRec blank{};
-  blank.amax = -INFINITY;
   blank.alpha = -INFINITY;
   hs.tile.assign((size_t)sh.ntiles, blank);
   for (int t = 0; t < sh.ntiles; ++t) {
@@ -325,11 +324,19 @@ void build_side(const float* pts, const double* w, int count, int dim, const dou
 
 
 
+// Skip gate of a sweep over n inputs: a tile whose bound lies more than
+// T = 30 + ceil(log2 n) (at most 64) below an output's running shift M is
+// skipped.  Every output's sum is at least 2^M (the term that set M is
+// summed), and the skipped terms add at most n 2^{M-T} <= 2^{M-30}: 1/64 of
+// float32's half-ulp, below the rounding of the float32 sum itself.
+double skip_depth(int n) { return std::min(64.0, 30.0 + std::ceil(std::log2((double)std::max(n, 1)))); }
+
 void fill_ctx(bdrs_solver s) {
   const Layout& L = s->L;
   char* base = (char*)s->prm.workspace;
   LaunchCtx& c = s->ctx;
   c.stream = (hipStream_t)s->prm.stream;
+  c.scale = s->prm.cost_scale;
   c.dim = s->prm.dim;
   c.splits_row = L.splits_row;
   c.splits_col = L.splits_col;
@@ -340,6 +347,7 @@ void fill_ctx(bdrs_solver s) {
     sd.ntiles = sh.ntiles;
     sd.np = sh.np;
     sd.pad = 0;
+    sd.tskip = skip_depth(sh.count);
     sd.abs = (float*)(base + abs);
     sd.off = (float*)(base + off);
     sd.tile = (TileRec*)(base + tile);
@@ -406,45 +414,48 @@ bdrs_status hip_status(hipError_t e, const char* what) {
   return BDRS_OK;
 }
 
-// one LSE sweep launch, bracketed by HIP events when profiling is on; a
-// profiled sweep also counts the input tiles its wavefronts evaluated
-hipError_t sweep(bdrs_solver s, bool transpose, bool cert, int splits, double eps_arg, int kofs = 0) {
-  if (!s->prof) return launch_sweep(s->ctx, transpose, cert, splits, eps_arg, kofs);
-  while (s->ev_pool.size() < s->ev_used + 2) {
-    hipEvent_t ev;
-    hipError_t e = hipEventCreate(&ev);
-    if (e != hipSuccess) return e;
-    s->ev_pool.push_back(ev);
-  }
-  char* base = (char*)s->prm.workspace;
+// One half iteration: an LSE sweep and its epilogue.  With profiling on, the
+// sweep's launch records its own start and end in a pair of HIP events and its
+// wavefronts count the input tiles they evaluate.
+hipError_t sweep(bdrs_solver s, bool transpose, bool cert, FinishKind kind, int splits, double eps_arg,
+                 double* lse_out = nullptr, int kofs = 0) {
   LaunchCtx c = s->ctx;
-  c.tile_count = (unsigned*)(base + s->L.tile_count);
-  c.tile_total = (unsigned long long*)(base + s->L.tile_total);
-  // the launch records the events at the kernel's own start and end
-  c.ev_start = s->ev_pool[s->ev_used];
-  c.ev_stop = s->ev_pool[s->ev_used + 1];
-  hipError_t e = launch_sweep(c, transpose, cert, splits, eps_arg, kofs);
-  const int np_out = transpose ? c.cols.np : c.rows.np;
-  if (e == hipSuccess) e = launch_count_tiles(c, splits * (np_out / kTile));
-  if (e == hipSuccess) {
-    s->ev_used += 2;
-    s->prof_sweeps += 1;
-    s->prof_entries += (double)s->prm.m * (double)s->prm.n;
+  if (s->prof) {
+    while (s->ev_pool.size() < s->ev_used + 2) {
+      hipEvent_t ev;
+      hipError_t e = hipEventCreate(&ev);
+      if (e != hipSuccess) return e;
+      s->ev_pool.push_back(ev);
+    }
+    char* base = (char*)s->prm.workspace;
+    c.tile_count = (unsigned*)(base + s->L.tile_count);
+    c.tile_total = (unsigned long long*)(base + s->L.tile_total);
+    // the launch records the events at the kernel's own start and end
+    c.ev_start = s->ev_pool[s->ev_used];
+    c.ev_stop = s->ev_pool[s->ev_used + 1];
   }
+  hipError_t e = launch_sweep(c, transpose, cert, splits, eps_arg, kofs);
+  if (s->prof) {
+    // one count per wavefront
+    if (e == hipSuccess) e = launch_count_tiles(c, splits * ((transpose ? c.cols.np : c.rows.np) / kTile));
+    if (e == hipSuccess) {
+      s->ev_used += 2;
+      s->prof_sweeps += 1;
+      s->prof_entries += (double)s->prm.m * (double)s->prm.n;
+    }
+  }
+  if (e == hipSuccess) e = launch_finish(s->ctx, transpose, kind, splits, lse_out, kofs);
   return e;
 }
 
 // one iteration of Algorithm 1; with cert the column sweep also gathers Algorithm 2's statistics
 bdrs_status enqueue_iteration(bdrs_solver s, bool cert, int kofs) {
-  const LaunchCtx& c = s->ctx;
   hipError_t e;
-  if ((e = sweep(s, false, false, s->L.splits_row, -1.0, kofs)) != hipSuccess) return hip_status(e, "row sweep");
-  if ((e = launch_finish(c, false, kFinishRow, s->L.splits_row, -1.0, nullptr, kofs)) != hipSuccess)
-    return hip_status(e, "row finish");
-  if ((e = sweep(s, true, cert, s->L.splits_col, -1.0, kofs)) != hipSuccess) return hip_status(e, "col sweep");
-  if ((e = launch_finish(c, true, cert ? kFinishColCert : kFinishCol, s->L.splits_col, -1.0, nullptr, kofs)) !=
+  if ((e = sweep(s, false, false, kFinishRow, s->L.splits_row, -1.0, nullptr, kofs)) != hipSuccess)
+    return hip_status(e, "row sweep");
+  if ((e = sweep(s, true, cert, cert ? kFinishColCert : kFinishCol, s->L.splits_col, -1.0, nullptr, kofs)) !=
       hipSuccess)
-    return hip_status(e, "col finish");
+    return hip_status(e, "col sweep");
   s->packed_rows = true;
   return BDRS_OK;
 }
@@ -555,12 +566,10 @@ bdrs_status read_cert(bdrs_solver s, bool repair, bdrs_cert* out) {
 bdrs_status enqueue_cert_only(bdrs_solver s) {
   bdrs_status st;
   if ((!s->packed_rows || separate_cert(s)) && (st = repack(s)) != BDRS_OK) return st;
-  const LaunchCtx& c = s->ctx;
   const double eps = eps_row_at(s, s->k - 1);
   hipError_t e;
-  if ((e = sweep(s, true, true, s->L.splits_col, eps)) != hipSuccess) return hip_status(e, "cert sweep");
-  if ((e = launch_finish(c, true, kFinishCertOnly, s->L.splits_col, eps, nullptr, 0)) != hipSuccess)
-    return hip_status(e, "cert finish");
+  if ((e = sweep(s, true, true, kFinishCertOnly, s->L.splits_col, eps)) != hipSuccess)
+    return hip_status(e, "cert sweep");
   return BDRS_OK;
 }
 
@@ -569,9 +578,8 @@ bdrs_status enqueue_repair(bdrs_solver s) {
   hipError_t e;
   const double eps = eps_row_at(s, s->k - 1);
   if ((e = launch_repair_pack(c)) != hipSuccess) return hip_status(e, "repair pack");
-  if ((e = sweep(s, false, false, s->L.splits_row, eps)) != hipSuccess) return hip_status(e, "repair sweep");
-  if ((e = launch_finish(c, false, kFinishRepair, s->L.splits_row, eps, nullptr, 0)) != hipSuccess)
-    return hip_status(e, "repair finish");
+  if ((e = sweep(s, false, false, kFinishRepair, s->L.splits_row, eps)) != hipSuccess)
+    return hip_status(e, "repair sweep");
   if ((e = launch_repair_reduce(c)) != hipSuccess) return hip_status(e, "repair reduce");
   if ((e = launch_prologue(c)) != hipSuccess) return hip_status(e, "prologue");  // restore cols.A
   return BDRS_OK;
@@ -1265,8 +1273,7 @@ bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps, const double*
   if ((e = launch_pack(c, tr, w, eps)) != hipSuccess) return hip_status(e, "pack");
   bdrs_status st = sync_k(s);
   if (st != BDRS_OK) return st;
-  if ((e = sweep(s, tr, false, splits, eps)) != hipSuccess) return hip_status(e, "sweep");
-  if ((e = launch_finish(c, tr, kFinishLse, splits, eps, out, 0)) != hipSuccess) return hip_status(e, "finish");
+  if ((e = sweep(s, tr, false, kFinishLse, splits, eps, out)) != hipSuccess) return hip_status(e, "sweep");
   s->packed_rows = false;
   return repack(s);
 }
@@ -1282,12 +1289,11 @@ bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col
   hipError_t e;
   if ((e = launch_pack_state(c, false, eps)) != hipSuccess) return hip_status(e, "pack beta");
   if ((e = launch_sweep_bary(c, s->L.splits_row, eps)) != hipSuccess) return hip_status(e, "row sweep");
-  if ((e = launch_finish(c, false, kFinishPlanRow, s->L.splits_row, eps, bary, 0)) != hipSuccess)
+  if ((e = launch_finish(c, false, kFinishPlanRow, s->L.splits_row, bary, 0)) != hipSuccess)
     return hip_status(e, "row finish");
   if ((e = launch_pack_state(c, true, eps)) != hipSuccess) return hip_status(e, "pack alpha");
-  if ((e = sweep(s, true, false, s->L.splits_col, eps)) != hipSuccess) return hip_status(e, "column sweep");
-  if ((e = launch_finish(c, true, kFinishPlanCol, s->L.splits_col, eps, nullptr, 0)) != hipSuccess)
-    return hip_status(e, "column finish");
+  if ((e = sweep(s, true, false, kFinishPlanCol, s->L.splits_col, eps)) != hipSuccess)
+    return hip_status(e, "column sweep");
   if ((e = launch_plan_stats(c)) != hipSuccess) return hip_status(e, "statistics");
   // tile order -> caller order
   if (row_marg && (e = launch_scatter(c.plan_row, c.rows.perm, c.rows.count, row_marg, c.stream)) != hipSuccess)
@@ -1321,19 +1327,16 @@ bdrs_status enqueue_round(bdrs_solver s, double eps) {
   hipError_t e;
   // 1: row sums of X and x = min(1, r / X 1)
   if ((e = launch_pack_state(c, false, eps)) != hipSuccess) return hip_status(e, "pack beta");
-  if ((e = sweep(s, false, false, s->L.splits_row, eps)) != hipSuccess) return hip_status(e, "row sweep");
-  if ((e = launch_finish(c, false, kFinishRound1, s->L.splits_row, eps, nullptr, 0)) != hipSuccess)
-    return hip_status(e, "row finish");
+  if ((e = sweep(s, false, false, kFinishRound1, s->L.splits_row, eps)) != hipSuccess)
+    return hip_status(e, "row sweep");
   // 2: column sums of diag(x) X and y = min(1, c / .)
   if ((e = launch_pack_state(c, true, eps, true)) != hipSuccess) return hip_status(e, "pack alpha x");
-  if ((e = sweep(s, true, false, s->L.splits_col, eps)) != hipSuccess) return hip_status(e, "column sweep");
-  if ((e = launch_finish(c, true, kFinishRound2, s->L.splits_col, eps, nullptr, 0)) != hipSuccess)
-    return hip_status(e, "column finish");
+  if ((e = sweep(s, true, false, kFinishRound2, s->L.splits_col, eps)) != hipSuccess)
+    return hip_status(e, "column sweep");
   // 3: row sums and cost of diag(x) X diag(y)
   if ((e = launch_pack_state(c, false, eps, true)) != hipSuccess) return hip_status(e, "pack beta y");
-  if ((e = sweep(s, false, true, s->L.splits_row, eps)) != hipSuccess) return hip_status(e, "cost sweep");
-  if ((e = launch_finish(c, false, kFinishRound3, s->L.splits_row, eps, nullptr, 0)) != hipSuccess)
-    return hip_status(e, "cost finish");
+  if ((e = sweep(s, false, true, kFinishRound3, s->L.splits_row, eps)) != hipSuccess)
+    return hip_status(e, "cost sweep");
   if ((e = launch_round_reduce(c)) != hipSuccess) return hip_status(e, "reduce");
   s->packed_rows = false;
   return BDRS_OK;

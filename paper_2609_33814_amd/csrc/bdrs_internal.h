@@ -42,14 +42,13 @@ struct Ctrl {
 // Everything the sweep needs to know about one input tile besides the offsets
 // and weights of its points, read with a single 64-byte scalar load.
 struct alignas(64) TileRec {
-  double amax;    // tile maximum of w2 - kappa2 |b|^2 (float64; -inf: no mass)
   double alpha;   // intercept of the plane fit of the tile's log2 weights w2 over the
-                  // offsets b: w2 <= alpha + gamma . b + rho for every point of the tile
-  float ctr[3];   // tile centre (relative to the common origin)
-  float rad[3];   // per-dimension radius of the offsets
-  float gam[3];   // plane-fit gradient gamma
-  float rho;      // largest residual of the fit, rounded up
-  float pad[2];
+                  // offsets b: w2 <= alpha + gam . b + rho (-inf: no mass)
+  float ctr[3];   // tile centre
+  float rad[3];   // max |offset| per dimension
+  float gam[3];   // gradient of the plane fit
+  float rho;      // largest residual of the plane fit, rounded up
+  int unused[4];
 };
 static_assert(sizeof(TileRec) == 64, "one scalar dwordx16 load per tile");
 
@@ -76,7 +75,7 @@ struct SideDev {
   float* off;      // [ntiles][dim][64] offsets from the tile centre
   float* A;        // [np] log2 weights of the next sweep that reads this side minus their
                    //      tile's plane fit and the tile-local quadratic (float32)
-  TileRec* tile;   // [ntiles] per-tile record (maximum, plane fit, centre, radius)
+  TileRec* tile;   // [ntiles] per-tile record (plane fit, centre, radius)
   const TileGeom* geom;  // [ntiles] geometry of the real points
   int* perm;       // [np] original index of each slot
   int* iperm;      // [count] slot of each original index
@@ -84,6 +83,7 @@ struct SideDev {
                    //      input point whose term is near the output's maximum, or -1
   double* marg;    // [np] marginal (r or c), 0 on padding
   double* logmarg; // [np] log marginal
+  double tskip;    // depth T of the skip gate of a sweep with this side as input
 };
 
 // Dual state (float64, tile order; O(m + n)).
@@ -161,6 +161,7 @@ enum FinishKind {
 
 struct LaunchCtx {
   hipStream_t stream;
+  double scale;    // cost scale s
   int dim;
   int splits_row, splits_col;  // input splits of the row / column sweep
   Ctrl* ctrl;
@@ -196,8 +197,8 @@ struct BatchItem {
 // An iteration's sweeps (eps_arg <= 0) take the row update's temperature when
 // the rows are the outputs and the column update's otherwise.
 hipError_t launch_sweep(const LaunchCtx& c, bool transpose, bool cert, int splits, double eps_arg, int kofs);
-hipError_t launch_finish(const LaunchCtx& c, bool transpose, FinishKind kind, int splits,
-                         double eps_arg, double* lse_out, int kofs);
+hipError_t launch_finish(const LaunchCtx& c, bool transpose, FinishKind kind, int splits, double* lse_out,
+                         int kofs);
 hipError_t launch_advance(Ctrl* ctrl, int n, hipStream_t s);
 hipError_t launch_prologue(const LaunchCtx& c);                       // lt and A_C for iteration k
 hipError_t launch_pack(const LaunchCtx& c, bool transpose, const double* w, double eps);

@@ -13,7 +13,8 @@
 //     w2_q - kappa2 |a - b_q|^2 = base + B . b_q + A_q,
 //     base = alpha - kappa2 |a|^2,  B = gamma + 2 kappa2 a,
 //     A_q = w2_q - alpha - gamma . b_q - kappa2 |b_q|^2   (written by the producing epilogue),
-// i.e. d FMAs and one add per entry, then one v_exp_f32 and one add.
+// i.e. d FMAs and one add per entry, then one v_exp_f32 and one add.  For d > 1
+// the plain sweep forms the exponents on the matrix cores (sweep_split_mfma).
 //
 // Precision split.  The weights w grow like g / eps as the temperature falls,
 // so float32 values of that size would carry absolute errors u |g| / eps.  The
@@ -28,7 +29,7 @@
 // temperature is 2 kappa2 |a| r, the transport distance |a| times larger.
 //
 // Stability without a per-entry max: the per-(output, tile) upper bound
-//     UB = base + sum_d |2 kappa2 a_d| rad_d  >=  max_q exponent
+//     UB >= max_q exponent  (lane_bound)
 // is compared with M.  Only when UB > M + 64 does the lane take the exact
 // maximum of the tile first (and rescale its sum), so every summed term is at
 // most 2^64 and M never exceeds the true maximum (no underflow of the leading
@@ -57,30 +58,51 @@ constexpr double kLn2D = 0.69314718055994530942;
 // this takes its exact maximum first, so no summed term exceeds 2^64.
 constexpr float kThresh = 64.0f;
 
-// Skip gate of a sweep over n inputs: a tile whose bound lies more than
-// T = 30 + ceil(log2 n) (at most 64) below an output's running shift M is
-// skipped.  Every output's sum is at least 2^M (the term that set M is
-// summed), and the skipped terms add at most n 2^{M-T} <= 2^{M-30}: 1/64 of
-// float32's half-ulp, below the rounding of the float32 sum itself.
-__device__ __forceinline__ double skip_threshold(int n) {
-  return fmin(64.0, 30.0 + ceil(log2((double)max(n, 1))));
+// Quotient of normal float64 numbers: two Newton steps on the hardware
+// reciprocal and one correction of the quotient, which rounds it as a division
+// does (the library's sequence also scales extreme operands; it is a third of a
+// wavefront's start-up arithmetic).
+__device__ __forceinline__ double fast_rcp(double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(fma(-b, r, 1.0), r, r);
+  return fma(fma(-b, r, 1.0), r, r);
+}
+__device__ __forceinline__ double fast_div(double a, double b) {
+  const double r = fast_rcp(b), q = a * r;
+  return fma(fma(-b, q, a), r, q);
 }
 
-template <typename CtrlPtr>
-__device__ __forceinline__ double eps_of(CtrlPtr c, double eps_arg, int kshift) {
-  if (eps_arg > 0.0) return eps_arg;
-  return c->eta / (c->lam * (double)(c->k + kshift) + 1.0);  // eta_k = eta / (lambda k + 1)
+// The control block in one scalar load, issued as soon as its address is known
+// (read field by field under conditions it cost a chain of round trips).
+typedef __attribute__((address_space(4))) const Ctrl cctrl;
+struct CtrlVals {
+  double eta, lam, scale;
+  long long k;  // of this launch's iteration
+  unsigned variant;
+};
+__device__ __forceinline__ CtrlVals load_ctrl(const Ctrl* c, int kofs) {
+  cctrl* p = (cctrl*)c;
+  CtrlVals v;
+  v.k = p->k + kofs;
+  v.variant = p->variant;
+  v.eta = p->eta;
+  v.lam = p->lam;
+  v.scale = p->scale;
+  return v;
 }
 
-// Temperature of the row update: eta_k, or eta / k for the old kernel K^{.k}.
-template <typename CtrlPtr>
-__device__ __forceinline__ double eps_row_of(CtrlPtr c, double eps_arg, int kshift) {
-  if (eps_arg > 0.0) return eps_arg;
-  if (c->variant & kVarOldKernel) {
-    const long long k = c->k + kshift;
-    return k >= 1 ? c->eta / (double)k : c->eta * kFarTemperature;
-  }
-  return eps_of(c, -1.0, kshift);
+// kappa2 = log2(e) s / eps of the column update of iteration k + ahead, at
+// eta_k = eta / (lambda k + 1).
+__device__ __forceinline__ double kap2_col(const CtrlVals& c, int ahead = 0) {
+  return fast_div(kLog2eD * c.scale, fast_div(c.eta, c.lam * (double)(c.k + ahead) + 1.0));
+}
+
+// The same of the row update: eta_k, or eta / k for the old kernel K^{.k} (at
+// k = 0 a temperature at which every cost term vanishes).
+__device__ __forceinline__ double kap2_row(const CtrlVals& c, int ahead = 0) {
+  if (!(c.variant & kVarOldKernel)) return kap2_col(c, ahead);
+  const long long k = c.k + ahead;
+  return fast_div(kLog2eD * c.scale, k >= 1 ? fast_div(c.eta, (double)k) : c.eta * kFarTemperature);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -130,6 +152,22 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
     v[i] = (read_lane(v[i], 0) + read_lane(v[i], 16)) + (read_lane(v[i], 32) + read_lane(v[i], 48));
 }
 
+// Wavefront maximum of a float (every lane receives it).
+template <int CTRL>
+__device__ __forceinline__ float dpp_movef(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float read_lanef(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ float wave_maxf(float v) {
+  v = fmaxf(v, dpp_movef<kDppXor1>(v));
+  v = fmaxf(v, dpp_movef<kDppXor2>(v));
+  v = fmaxf(v, dpp_movef<kDppHalfMirror>(v));
+  v = fmaxf(v, dpp_movef<kDppMirror>(v));
+  return fmaxf(fmaxf(read_lanef(v, 0), read_lanef(v, 16)), fmaxf(read_lanef(v, 32), read_lanef(v, 48)));
+}
+
 __device__ __forceinline__ double wave_max(double v) {
   v = fmax(v, dpp_move<kDppXor1>(v));
   v = fmax(v, dpp_move<kDppXor2>(v));
@@ -141,14 +179,14 @@ __device__ __forceinline__ double wave_max(double v) {
 // ---------------------------------------------------------------------------
 // Sweep
 // ---------------------------------------------------------------------------
-// Global-address-space views: the tile data is read through these so that
-// uniform reads compile to scalar loads also when the pointers come from a
-// descriptor in memory (batched launches), not only from kernel arguments.
-typedef __attribute__((address_space(1))) const float gfloat;
-typedef __attribute__((address_space(1))) const double gdouble;
-typedef __attribute__((address_space(1))) const Ctrl gctrl;
-
-typedef __attribute__((address_space(1))) const TileRec gtile;
+// Constant-address-space views of what a sweep only reads (the kernels before
+// it wrote it): uniform reads compile to scalar loads whatever pointer they
+// come from (kernel argument or a descriptor in memory) and whatever the kernel
+// has stored before.
+typedef __attribute__((address_space(4))) const float gfloat;
+typedef __attribute__((address_space(4))) const double gdouble;
+typedef __attribute__((address_space(4))) const int gint;
+typedef __attribute__((address_space(4))) const TileRec gtile;
 
 // Points of a tile per group: the tile data of one group (8 D offsets into
 // scalar registers, 8 weights into vector registers by broadcast loads) is
@@ -158,7 +196,7 @@ constexpr int kGroup = 8;
 // The fields of a tile record the sweep uses (dimensions < D).
 template <int D>
 struct TileVals {
-  double amax, alpha;
+  double alpha;
   float ctr[D], rad[D], gam[D], rho;
 };
 
@@ -167,15 +205,14 @@ __device__ __forceinline__ TileVals<D> load_tile(gtile* __restrict__ rec) {
   gdouble* dp = (gdouble*)rec;
   gfloat* fp = (gfloat*)rec;
   TileVals<D> v;
-  v.amax = dp[0];
-  v.alpha = dp[1];
+  v.alpha = dp[0];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    v.ctr[d] = fp[4 + d];
-    v.rad[d] = fp[7 + d];
-    v.gam[d] = fp[10 + d];
+    v.ctr[d] = fp[2 + d];
+    v.rad[d] = fp[5 + d];
+    v.gam[d] = fp[8 + d];
   }
-  v.rho = fp[13];
+  v.rho = fp[11];
   return v;
 }
 
@@ -200,238 +237,393 @@ __device__ __forceinline__ Group<D> load_group(gfloat* __restrict__ offs_t, gflo
   return r;
 }
 
-// One block of kSweepBlock outputs (bx) against one split of the input tiles
-// (every nsplit-th tile).  Per chunk of up to 64 tiles a coarse test against
-// the wavefront's output box picks the candidate tiles; per candidate the lane
-// bounds its own exponents and the wavefront skips the tile when no lane can
-// see it, else every lane evaluates z_q = cm + B . b_q + A_q and accumulates
-// exp2(z_q) (and, for the certificate, the cost-weighted sum).  The next group
-// of 8 points (after a tile's last group, the next candidate's first) is
-// requested before the current group is computed, so the loads overlap the
-// arithmetic.
-template <int D, int MODE>
-__device__ __forceinline__ void sweep_block(
-    gfloat* __restrict__ out_abs, int np_out,
-    gfloat* __restrict__ in_off, gfloat* __restrict__ in_A, gtile* __restrict__ in_tile,
-    int ntiles_in, int count_in, int nsplit, const int* __restrict__ hint,
-    void* __restrict__ part, double* __restrict__ part_ref, gctrl* __restrict__ ctrl, double eps_arg, int kofs,
-    int bx, int split, bool row_sweep, unsigned* __restrict__ tile_count, int slot) {
-  constexpr bool CERT = MODE == kSweepCert;
-  constexpr bool BARY = MODE == kSweepBary;
-  const int p = bx * kSweepBlock + threadIdx.x;
-  // Split `split` of nsplit takes every nsplit-th input tile (split, split +
-  // nsplit, ...), so that each split samples the whole input cloud: late in a
-  // solve only the tiles near an output block matter, and they spread over
-  // all splits instead of crowding into one wavefront's work.  Local index i
-  // is tile split + i nsplit; nt tiles in all.
-  const int nt = split < ntiles_in ? (ntiles_in - 1 - split) / nsplit + 1 : 0;
-  // the output point and its hint first: their loads do not wait for the
-  // temperature, whose control-block reads sit behind branches
-  float P[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) P[d] = out_abs[(size_t)d * np_out + p];
-  const int j_hint = hint[p];
-  const double eps = row_sweep ? eps_row_of(ctrl, eps_arg, kofs) : eps_of(ctrl, eps_arg, kofs);
-  const double kap2d = kLog2eD * ctrl->scale / eps;
-  const double kap2x2d = 2.0 * kap2d;
-  const float kap2f = (float)kap2d;
-  const float inv2kap = (float)(0.5 / kap2d);
+// The input side of a sweep.
+struct SweepIn {
+  gfloat* off;
+  gfloat* A;
+  gtile* tile;
+  int ntiles, count;
+};
 
-  // The wavefront's output box (all lanes, padding included: a larger box
-  // only loosens the coarse bound below) and the coarse bound of the first
-  // chunk of tiles, computed before the warm start so that their loads overlap
-  // its own.
-  const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
-  const int lane = (int)(threadIdx.x & (kTile - 1));
-  float blo[D], bhi[D];
+__device__ __forceinline__ SweepIn sweep_in(const SideDev& s) {
+  return SweepIn{(gfloat*)s.off, (gfloat*)s.A, (gtile*)s.tile, s.ntiles, s.count};
+}
+
+// What a lane keeps for its output while it sweeps: the point, the kernel's
+// temperature, the wavefront's output box (all lanes, padding included: a
+// larger box only loosens the coarse bound) and the skip gate's depth.
+template <int D>
+struct SweepOut {
+  float P[D], blo[D], bhi[D];
+  double kap2d, tskip;  // kappa2; depth T of the skip gate (SideDev::tskip)
+  float kap2f, inv2kap;
+};
+
+// The sums of one split of one output and the shift they are relative to.
+struct SplitSum {
+  double M;
+  float S, N, V[3];
+  int J;          // slot of the term that set the shift
+  int evaluated;  // input tiles this wavefront evaluated (the same on every lane)
+};
+
+// rec: the record of the outputs' own tile, whose box (widened against the
+// rounding of its centre and radius) holds the wavefront's 64 points.
+template <int D>
+__device__ __forceinline__ SweepOut<D> sweep_out(const float (&P)[D], gtile* rec, double kap2, double tskip) {
+  SweepOut<D> o;
+  o.kap2d = kap2;
+  o.kap2f = (float)kap2;
+  o.inv2kap = (float)(0.5 * fast_rcp(kap2));
+  o.tskip = tskip;
+  gfloat* fp = (gfloat*)rec;
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    blo[d] = (float)(-wave_max(-(double)P[d]));
-    bhi[d] = (float)wave_max((double)P[d]);
+    const float ctr = fp[2 + d], half = fp[5 + d] * 1.000001f + fabsf(ctr) * 1e-6f;
+    o.P[d] = P[d];
+    o.blo[d] = ctr - half;
+    o.bhi[d] = ctr + half;
   }
-  // Coarse test of up to 64 tiles at once, lane l taking tile c0 + l: an
-  // upper bound of the exponents of the tile's points for every output of the
-  // wavefront, alpha + sum_d |gamma_d| r_d + rho - kappa2 dist^2(output box,
-  // tile box), to be compared with the smallest running maximum of the
-  // wavefront.  It bounds each lane's own bound from above, so a tile it
-  // rejects would be skipped by the per-lane test too.  Local indices c0 ...
-  // c1-1; the tile index is clamped to a valid tile (also for an empty split).
-  auto coarse = [&](int c0, int c1) -> double {
-    const int il = max(min(c0 + lane, c1 - 1), 0);
-    gtile* rec = in_tile + min(split + il * nsplit, ntiles_in - 1);
-    gfloat* fp = (gfloat*)rec;
-    const double alpha = ((gdouble*)rec)[1];
-    float w = fp[13], g2 = 0.0f;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const float ctr = fp[4 + d], rad = fp[7 + d], gam = fp[10 + d];
-      w = fmaf(fabsf(gam), rad, w);
-      // gap between the boxes, shrunk by a relative 1e-5 against rounding
-      const float gap = fmaxf(0.0f, fmaxf((ctr - rad) - bhi[d], blo[d] - (ctr + rad))) * 0.99999f;
-      g2 = fmaf(gap, gap, g2);
-    }
-    return alpha + (double)fmaf(-kap2f, g2, w);
-  };
-  double cub = coarse(0, min(kTile, nt));
+  return o;
+}
 
-  // Warm start: the exact exponent of one remembered input point is a lower
-  // bound of the output's maximum over all inputs, so it is a valid shift for
-  // every split (a split whose terms all lie far below it adds ~nothing); it
-  // spares the exact-max pass on the first tile of each split.  Its loads are
-  // issued unconditionally at a clamped, valid index and the result is masked
-  // afterwards: loads under a branch would wait for their data one by one.
-  double M = -INFINITY;
-  int J = -1;
-  {
-    const int j = j_hint;
-    const int jc = min(max(j, 0), count_in - 1);
-    const int tj = jc / kTile, qj = jc % kTile;
-    const double al = in_tile[tj].alpha;
-    const float aj = in_A[jc];
-    double na = 0.0, ab = 0.0, gb = 0.0;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const double ad = (double)P[d] - (double)in_tile[tj].ctr[d];
-      const double bd = (double)in_off[((size_t)tj * D + d) * kTile + qj];
-      na += ad * ad;
-      ab += ad * bd;
-      gb += (double)in_tile[tj].gam[d] * bd;
-    }
-    if (j >= 0 && j < count_in && al > -INFINITY && aj > -INFINITY) {
-      M = al + (double)aj + gb + kap2d * (2.0 * ab - na);
-      J = j;
-    }
-  }
-  // the records' reference: the warm start's exponent (the same in every
-  // split), 0 without one; split 0 stores it for the merge
-  const double Rref = M > -INFINITY ? M : 0.0;
-  if (!BARY && split == 0) part_ref[p] = Rref;
-  float S = 0.0f, N = 0.0f;
-  float V[D];
-  // writes this split's record: the shift relative to the reference in
-  // float32, the sums rescaled by that rounding so that the record is exact
-  auto write_rec = [&]() {
-    float dM = -INFINITY, fix = 1.0f;
-    if (M > -INFINITY) {
-      const double dd = M - Rref;
-      dM = (float)dd;
-      fix = fast_exp2((float)(dd - (double)dM));
-    }
-    if (CERT) {
-      reinterpret_cast<PartialCert*>(part)[(size_t)split * np_out + p] = PartialCert{dM, S * fix, N * fix, J};
-    } else {
-      reinterpret_cast<PartialRec*>(part)[(size_t)split * np_out + p] = PartialRec{dM, S * fix, J};
-    }
-  };
-#pragma unroll
-  for (int d = 0; d < D; ++d) V[d] = 0.0f;
-  int evaluated = 0;  // input tiles this wavefront evaluated (the same on every lane)
-  if (nt == 0) {
-    if (tile_count && (threadIdx.x & (kTile - 1)) == 0) tile_count[slot] = 0;
-    if (BARY) {
-      PartialBary* pb = reinterpret_cast<PartialBary*>(part) + (size_t)split * np_out + p;
-      pb->M = M;
-      pb->S = S;
-      for (int d = 0; d < 3; ++d) pb->V[d] = 0.0f;
-    } else {
-      write_rec();
-    }
-    return;
-  }
+// Lower bound of the smallest skip gate of the wavefront: the minimum taken in
+// float32 and moved down by more than the conversion's rounding.
+__device__ __forceinline__ double gate_min(double Mlo) {
+  const float m = -wave_maxf(-(float)Mlo);
+  return (double)fmaf(-1e-6f, fabsf(m), m) - 1e-6;
+}
 
-  const double tskip = skip_threshold(count_in);
-  double Mth = M + kThresh;                     // the exact-max gate, updated with M
-  double Mlo = M - tskip;                       // the skip gate, updated with M
-  // The weights are read with broadcast vector loads (a lane-dependent zero in
-  // the address), which leaves the scalar path to the offsets and the
-  // candidates' tile records: moving either kind the other way measured slower.
+// Tiles of split `split`: split, split + nsplit, ... (local index i is tile
+// split + i nsplit), so that each split samples the whole input cloud: late in
+// a solve only the tiles near an output block matter, and they spread over all
+// splits instead of crowding into one wavefront's work.
+__device__ __forceinline__ int split_tiles(int ntiles, int split, int nsplit) {
+  return split < ntiles ? (ntiles - 1 - split) / nsplit + 1 : 0;
+}
+
+// Coarse test of up to 64 tiles at once, lane l taking local tile c0 + l: an
+// upper bound of the exponents of the tile's points for every output of the
+// wavefront, alpha + sum_d |gamma_d| r_d + rho - kappa2 dist^2(output box,
+// tile box), to be compared with the smallest running maximum of the
+// wavefront.  It bounds each lane's own bound from above, so a tile it
+// rejects would be skipped by the per-lane test too.  The tile index is
+// clamped to a valid tile (also for an empty split).
+template <int D>
+__device__ __forceinline__ double coarse_of(const TileVals<D>& t, const SweepOut<D>& o) {
+  float w = t.rho, g2 = 0.0f;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    w = fmaf(fabsf(t.gam[d]), t.rad[d], w);
+    // gap between the boxes, shrunk by a relative 1e-5 against rounding
+    const float gap =
+        fmaxf(0.0f, fmaxf((t.ctr[d] - t.rad[d]) - o.bhi[d], o.blo[d] - (t.ctr[d] + t.rad[d]))) * 0.99999f;
+    g2 = fmaf(gap, gap, g2);
+  }
+  return t.alpha + (double)fmaf(-o.kap2f, g2, w);
+}
+
+// Candidates among local tiles c0 ... c1-1 of a split, as a bit mask.
+template <int D>
+__device__ __forceinline__ unsigned long long coarse_mask(const SweepIn& in, const SweepOut<D>& o, double gate,
+                                                          int split, int nsplit, int c0, int c1) {
+  const int lane = (int)(threadIdx.x & (kTile - 1));
+  const int il = max(min(c0 + lane, c1 - 1), 0);
+  const double cub = coarse_of<D>(load_tile<D>(in.tile + min(split + il * nsplit, in.ntiles - 1)), o);
+  return __ballot(c0 + lane < c1 && !(cub < gate));
+}
+
+// Warm start: the exact exponent of one remembered input point is a lower
+// bound of the output's maximum over all inputs, so it is a valid shift for
+// every split (a split whose terms all lie far below it adds ~nothing); it
+// spares the exact-max pass on the first tile of each split.  Its loads are
+// issued unconditionally at a clamped, valid index and the result is masked
+// afterwards: loads under a branch would wait for their data one by one.
+template <int D>
+__device__ __forceinline__ void warm_start(const SweepIn& in, const SweepOut<D>& o, int j, double& M, int& J) {
+  M = -INFINITY;
+  J = -1;
+  const int jc = min(max(j, 0), in.count - 1);
+  const int tj = jc / kTile, qj = jc % kTile;
+  const double al = in.tile[tj].alpha;
+  const float aj = in.A[jc];
+  double na = 0.0, ab = 0.0, gb = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const double ad = (double)o.P[d] - (double)in.tile[tj].ctr[d];
+    const double bd = (double)in.off[((size_t)tj * D + d) * kTile + qj];
+    na += ad * ad;
+    ab += ad * bd;
+    gb += (double)in.tile[tj].gam[d] * bd;
+  }
+  if (j >= 0 && j < in.count && al > -INFINITY && aj > -INFINITY) {
+    M = al + (double)aj + gb + o.kap2d * (2.0 * ab - na);
+    J = j;
+  }
+}
+
+// Upper bound of the exponents w2_q - kappa2 |a - b_q|^2 of a tile:
+// w2_q <= alpha + gamma . b_q + rho, and the concave quadratic
+// gamma . b - kappa2 |a - b|^2 is maximised over the tile's box per axis.
+template <int D>
+__device__ __forceinline__ double lane_bound(const TileVals<D>& t, const SweepOut<D>& o, const float (&a)[D]) {
+  float ubf = t.rho;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const float g = t.gam[d], rad = t.rad[d];
+    const float bs = __builtin_amdgcn_fmed3f(fmaf(g, o.inv2kap, a[d]), -rad, rad);  // clamp to the box
+    const float df = a[d] - bs;
+    ubf = fmaf(g, bs, ubf);
+    ubf = fmaf(-o.kap2f, df * df, ubf);
+  }
+  return t.alpha + (double)ubf;
+}
+
+// Exact maximum of a tile's exponents (relative to base) and its point.
+template <int D>
+__device__ __forceinline__ float tile_max(gfloat* __restrict__ offs, gfloat* __restrict__ Aq, const float (&B)[D],
+                                          int& qi) {
+  float tm = -INFINITY;
+  qi = 0;
+#pragma unroll 8
+  for (int q = 0; q < kTile; ++q) {
+    float z = Aq[q];
+#pragma unroll
+    for (int d = 0; d < D; ++d) z = fmaf(B[d], offs[d * kTile + q], z);
+    if (z > tm) {
+      tm = z;
+      qi = q;
+    }
+  }
+  return tm;
+}
+
+// One split of the plain sweep for one wavefront of 64 outputs, the exponents
+// formed on the matrix cores.  Per chunk of up to 64 tiles the coarse test
+// picks the candidates; per candidate the lane bounds its own exponents, the
+// wavefront skips the tile when no lane can see it, else the whole 64 x 64
+// block of exponents z_qp = cm_p + B_p . b_q + A_q is a product of inner
+// dimension D + 2, taken in rank-one steps of v_mfma_f32_32x32x1 (two blocks
+// of 32 outputs, 32 inputs): each step is one IEEE fused multiply-add per
+// element, so the chain cm, + B_0 b_0, ..., + 1 A_q rounds exactly as the
+// scalar code of the other modes does.  Input operands: lane l holds point
+// pt(l) of the tile, one coalesced load per coordinate, and cbsz/abid
+// broadcast either half of them to both blocks.  Result element i of a block
+// is row 8 (i / 4) + 4 (lane / 32) + i % 4; with bits 1 and 2 of the point
+// index swapped (pt) the lower half wave holds the points q = 0, 1 mod 4 and
+// the upper half q = 2, 3 mod 4, in order, so each lane's two running sums per
+// output are the sums over q mod 4 in point order and one exchange between
+// the half waves (v_permlane32_swap) brings the four together.
+//
+// Bound: the float32 VALU / matrix pipe, one for both on gfx950 (work of the
+// two kinds from different wavefronts takes the sum of their times).  Measured
+// cycles per wavefront instruction: fused multiply-add 4.2 (any form with three
+// register operands or a scalar one), exp2 8.2, add 2.5 (4 after an exp2),
+// rank-one step 2.03 per input.  So an entry takes 20.9 cycles here against
+// 25.8 on the VALU for d = 3, 18.8 against 21.6 for d = 2, 16.8 against 17.4
+// for d = 1; and the tile data comes by one vector load per coordinate instead
+// of a chain of scalar ones.  Dense sweeps of 1 M points per side (d = 3):
+// 194 -> 173 ms; 50 iterations of two 251x251 grids (d = 2, 7% of the entries):
+// 9.46 -> 8.48 ms.  For d = 1 the two are even on paper and the VALU form,
+// which needs fewer registers, measured 3% faster (30000 x 20000 points, 50
+// iterations: 5.53 against 5.69 ms), so only d > 1 comes here.  The next
+// candidate's record and points are requested while the current one is tested
+// and evaluated.  Five wavefronts per SIMD (kSweepWaves) measured best: four
+// 2% slower, seven and eight spill or lose the overlap of the two halves.
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+template <int D>
+struct TilePts {
+  float b[D], a;
+};
+
+template <int D>
+__device__ __forceinline__ TilePts<D> load_points(const SweepIn& in, int t, int pt) {
+  TilePts<D> v;
+#pragma unroll
+  for (int d = 0; d < D; ++d) v.b[d] = in.off[((size_t)t * D + d) * kTile + pt];
+  v.a = in.A[(size_t)t * kTile + pt];
+  return v;
+}
+
+// Exponents of 32 inputs (half H of the tile's points) against 64 outputs.
+template <int D, int H>
+__device__ __forceinline__ f32x32 exponents(const TilePts<D>& q, const float (&B)[D], float cm) {
+  f32x32 z = {};
+  z = __builtin_amdgcn_mfma_f32_32x32x1f32(1.0f, cm, z, 1, H, 0);
+#pragma unroll
+  for (int d = 0; d < D; ++d) z = __builtin_amdgcn_mfma_f32_32x32x1f32(q.b[d], B[d], z, 1, H, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x1f32(q.a, 1.0f, z, 1, H, 0);
+}
+
+// sum_q 2^{z_q} over the tile's 64 points for the lane's own output.
+template <int D>
+__device__ __forceinline__ float tile_sum(const TilePts<D>& pts, const float (&B)[D], float cm) {
+  // block 0 (outputs 0-31): x0, x1; block 1 (outputs 32-63): y0, y1
+  f32x32 z = exponents<D, 0>(pts, B, cm);
+  float x0 = fast_exp2(z[0]), x1 = fast_exp2(z[1]), y0 = fast_exp2(z[16]), y1 = fast_exp2(z[17]);
+#pragma unroll
+  for (int i = 2; i < 16; i += 2) {
+    x0 += fast_exp2(z[i]);
+    x1 += fast_exp2(z[i + 1]);
+    y0 += fast_exp2(z[16 + i]);
+    y1 += fast_exp2(z[17 + i]);
+  }
+  z = exponents<D, 1>(pts, B, cm);
+#pragma unroll
+  for (int i = 0; i < 16; i += 2) {
+    x0 += fast_exp2(z[i]);
+    x1 += fast_exp2(z[i + 1]);
+    y0 += fast_exp2(z[16 + i]);
+    y1 += fast_exp2(z[17 + i]);
+  }
+  // lower lanes hold q = 0, 1 mod 4 and upper lanes q = 2, 3 mod 4 of outputs
+  // lane % 32 (x) and 32 + lane % 32 (y): after the swap each lane has both
+  // pairs of its own output
+  const u32x2 w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0 + x1), __float_as_uint(y0 + y1), false, false);
+  return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+
+// Exponent of a tile for a lane: slope B = gamma + 2 kappa2 a (rounded once)
+// and base = alpha - kappa2 |a|^2.
+template <int D>
+__device__ __forceinline__ double tile_base(const TileVals<D>& t, const SweepOut<D>& o, const float (&a)[D],
+                                            float (&B)[D]) {
+  const double kap2x2 = 2.0 * o.kap2d;
+  float na = 0.0f;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    na = fmaf(a[d], a[d], na);
+    B[d] = (float)fma(kap2x2, (double)a[d], (double)t.gam[d]);
+  }
+  return t.alpha - o.kap2d * (double)na;
+}
+
+template <int D>
+__device__ __forceinline__ SplitSum sweep_split_mfma(const SweepIn& in, const SweepOut<D>& o, int split, int nsplit,
+                                                      double M, int J, unsigned long long cand) {
+  const int lane = (int)(threadIdx.x & (kTile - 1));
+  const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
+  const int pt = (lane & ~6) | ((lane & 2) << 1) | ((lane & 4) >> 1);
+  const int nt = split_tiles(in.ntiles, split, nsplit);
+  SplitSum r{M, 0.0f, 0.0f, {0.0f, 0.0f, 0.0f}, J, 0};
+  double Mth = M + kThresh;      // the exact-max gate, updated with M
+  double Mlo = M - o.tskip;      // the skip gate, updated with M
+  for (int c0 = 0; c0 < nt; c0 += kTile) {
+    const int c1 = min(c0 + kTile, nt);
+    if (c0 != 0) cand = coarse_mask<D>(in, o, gate_min(Mlo), split, nsplit, c0, c1);
+    if (!cand) continue;
+    int t = split + (c0 + __builtin_ctzll(cand)) * nsplit;
+    TileVals<D> cur = load_tile<D>(in.tile + t);
+    TilePts<D> pts = load_points<D>(in, t, pt);
+    while (cand) {
+      cand &= cand - 1;
+      const int tn = cand ? split + (c0 + __builtin_ctzll(cand)) * nsplit : t;  // the last re-reads itself
+      const TileVals<D> nxt = load_tile<D>(in.tile + tn);
+      const TilePts<D> nps = load_points<D>(in, tn, pt);
+      float a[D];
+#pragma unroll
+      for (int d = 0; d < D; ++d) a[d] = o.P[d] - cur.ctr[d];
+      const double ub = lane_bound<D>(cur, o, a);
+      // every term of this tile lies below 2^-T of the running maximum on every
+      // lane: the tile cannot change any sum in float32, so it is skipped, as
+      // is a tile without mass (alpha = -inf)
+      if (!(__all(ub < Mlo) || __double_as_longlong(cur.alpha) == (long long)0xFFF0000000000000ULL)) {
+        ++r.evaluated;
+        float B[D];
+        const double base = tile_base<D>(cur, o, a, B);
+        if (ub > Mth) {
+          // exact maximum of this tile for the lanes whose bound exceeds the window
+          int qi;
+          const double tmd = base + (double)tile_max<D>(in.off + (size_t)t * D * kTile,
+                                                        in.A + (size_t)t * kTile + lane0, B, qi);
+          if (tmd > r.M) {
+            r.S *= fast_exp2((float)(r.M - tmd));
+            r.M = tmd;
+            Mth = r.M + kThresh;
+            Mlo = r.M - o.tskip;
+            r.J = t * kTile + qi;
+          }
+        }
+        r.S += tile_sum<D>(pts, B, (float)(base - r.M));
+      }
+      t = tn;
+      cur = nxt;
+      pts = nps;
+    }
+  }
+  return r;
+}
+
+// The same walk with every entry evaluated on the VALU: the certificate sweep
+// (cost-weighted sum N) and the barycentric sweep (coordinate sums V), whose
+// weighted sums need the points per entry, and the plain sweep for d = 1.  The
+// weights are read with broadcast vector loads (a lane-dependent zero in the
+// address), which leaves the scalar path to the offsets and the candidates'
+// tile records; the next group of 8 points (after a tile's last group, the
+// next candidate's first) is requested before the current group is computed.
+template <int D, int MODE>
+__device__ __forceinline__ SplitSum sweep_split_valu(const SweepIn& in, const SweepOut<D>& o, int split,
+                                                         int nsplit, double M, int J, unsigned long long cand) {
+  constexpr bool CERT = MODE == kSweepCert;
+  constexpr bool BARY = MODE == kSweepBary;
+  const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
+  const int nt = split_tiles(in.ntiles, split, nsplit);
+  SplitSum r{M, 0.0f, 0.0f, {0.0f, 0.0f, 0.0f}, J, 0};
+  double Mth = M + kThresh;      // the exact-max gate, updated with M
+  double Mlo = M - o.tskip;      // the skip gate, updated with M
   Group<D> grp;
   for (int c0 = 0; c0 < nt; c0 += kTile) {
     const int c1 = min(c0 + kTile, nt);
-    if (c0 != 0) cub = coarse(c0, c1);
-    const double mlo_min = -wave_max(-Mlo);
-    unsigned long long cand = __ballot(c0 + lane < c1 && !(cub < mlo_min));
+    if (c0 != 0) cand = coarse_mask<D>(in, o, gate_min(Mlo), split, nsplit, c0, c1);
     if (cand) {
       const int tf = split + (c0 + __builtin_ctzll(cand)) * nsplit;
-      grp = load_group<D>(in_off + (size_t)tf * D * kTile, in_A + (size_t)tf * kTile + lane0, 0);
+      grp = load_group<D>(in.off + (size_t)tf * D * kTile, in.A + (size_t)tf * kTile + lane0, 0);
     }
     while (cand) {
       const int t = split + (c0 + __builtin_ctzll(cand)) * nsplit;
       cand &= cand - 1;
-      const TileVals<D> cur = load_tile<D>(in_tile + t);
+      const TileVals<D> cur = load_tile<D>(in.tile + t);
       const int tn = cand ? split + (c0 + __builtin_ctzll(cand)) * nsplit : t;  // next candidate (the last re-reads itself)
       // tile addresses computed before any lane-dependent branch
-      gfloat* __restrict__ offs_t = in_off + (size_t)t * D * kTile;
-      gfloat* __restrict__ a_t = in_A + (size_t)t * kTile + lane0;
-      gfloat* __restrict__ offs_n = in_off + (size_t)tn * D * kTile;
-      gfloat* __restrict__ a_n = in_A + (size_t)tn * kTile + lane0;
+      gfloat* __restrict__ offs_t = in.off + (size_t)t * D * kTile;
+      gfloat* __restrict__ a_t = in.A + (size_t)t * kTile + lane0;
+      gfloat* __restrict__ offs_n = in.off + (size_t)tn * D * kTile;
+      gfloat* __restrict__ a_n = in.A + (size_t)tn * kTile + lane0;
       float a[D];
 #pragma unroll
-      for (int d = 0; d < D; ++d) a[d] = P[d] - cur.ctr[d];
-      // upper bound of the exponents w2_q - kappa2 |a - b_q|^2 of this tile:
-      // w2_q <= alpha + gamma . b_q + rho, and the concave quadratic
-      // gamma . b - kappa2 |a - b|^2 is maximised over the tile's box per axis
-      float ubf = cur.rho;
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const float g = cur.gam[d], rad = cur.rad[d];
-        const float bs = __builtin_amdgcn_fmed3f(fmaf(g, inv2kap, a[d]), -rad, rad);  // clamp to the box
-        const float df = a[d] - bs;
-        ubf = fmaf(g, bs, ubf);
-        ubf = fmaf(-kap2f, df * df, ubf);
-      }
-      const double ub = cur.alpha + (double)ubf;
+      for (int d = 0; d < D; ++d) a[d] = o.P[d] - cur.ctr[d];
+      const double ub = lane_bound<D>(cur, o, a);
       // every term of this tile lies below 2^-T of the running maximum on every
-      // lane: the tile cannot change any sum in float32, so it is skipped.  A
-      // tile without mass (alpha = -inf) is skipped here once M is finite, and
-      // by its maximum below; testing the maximum first would make every tile
-      // wait for two scalar round trips (the maximum, then the bound's fields)
-      if (__all(ub < Mlo) ||
-          __double_as_longlong(cur.amax) == (long long)0xFFF0000000000000ULL) {  // -inf: no mass
+      // lane: the tile cannot change any sum in float32, so it is skipped, as
+      // is a tile without mass (alpha = -inf)
+      if (__all(ub < Mlo) || __double_as_longlong(cur.alpha) == (long long)0xFFF0000000000000ULL) {
         grp = load_group<D>(offs_n, a_n, 0);
         continue;
       }
-      ++evaluated;
-      float B[D], na = 0.0f;
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        na = fmaf(a[d], a[d], na);
-        B[d] = (float)fma(kap2x2d, (double)a[d], (double)cur.gam[d]);  // gamma + 2 kappa2 a, rounded once
-      }
-      const double base = cur.alpha - kap2d * (double)na;  // alpha_t - kappa2 |a|^2
-
+      ++r.evaluated;
+      float B[D];
+      const double base = tile_base<D>(cur, o, a, B);
       if (ub > Mth) {
         // exact maximum of this tile for the lanes whose bound exceeds the window
-        gfloat* __restrict__ offs = offs_t;
-        gfloat* __restrict__ Aq = a_t;
-        float tm = -INFINITY;
-        int qi = 0;
-#pragma unroll 8
-        for (int q = 0; q < kTile; ++q) {
-          float z = Aq[q];
-#pragma unroll
-          for (int d = 0; d < D; ++d) z = fmaf(B[d], offs[d * kTile + q], z);
-          if (z > tm) {
-            tm = z;
-            qi = q;
-          }
-        }
-        const double tmd = base + (double)tm;
-        if (tmd > M) {
-          const float sc = fast_exp2((float)(M - tmd));
-          S *= sc;
-          if (CERT) N *= sc;
+        int qi;
+        const double tmd = base + (double)tile_max<D>(offs_t, a_t, B, qi);
+        if (tmd > r.M) {
+          const float sc = fast_exp2((float)(r.M - tmd));
+          r.S *= sc;
+          if (CERT) r.N *= sc;
           if (BARY) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) V[d] *= sc;
+            for (int d = 0; d < D; ++d) r.V[d] *= sc;
           }
-          M = tmd;
-          Mth = M + kThresh;
-          Mlo = M - tskip;
-          J = t * kTile + qi;
+          r.M = tmd;
+          Mth = r.M + kThresh;
+          Mlo = r.M - o.tskip;
+          r.J = t * kTile + qi;
         }
       }
-      const float cm = (float)(base - M);
+      const float cm = (float)(base - r.M);
       float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
       float n0 = 0.f, n1 = 0.f;
       float vt[D];
@@ -471,58 +663,118 @@ __device__ __forceinline__ void sweep_block(
         grp = nx;
       }
       const float st = (s0 + s1) + (s2 + s3);
-      S += st;
-      if (CERT) N += n0 + n1;
+      r.S += st;
+      if (CERT) r.N += n0 + n1;
       if (BARY) {
         // sum_q e_q y_q = c_t sum_q e_q + sum_q e_q b_q (points = tile centre + offset)
 #pragma unroll
-        for (int d = 0; d < D; ++d) V[d] += fmaf(cur.ctr[d], st, vt[d]);
+        for (int d = 0; d < D; ++d) r.V[d] += fmaf(cur.ctr[d], st, vt[d]);
       }
     }
   }
-  if (tile_count && (threadIdx.x & (kTile - 1)) == 0) tile_count[slot] = (unsigned)evaluated;
-  if (BARY) {
-    PartialBary* pb = reinterpret_cast<PartialBary*>(part) + (size_t)split * np_out + p;
-    pb->M = M;
-    pb->S = S;
-    for (int d = 0; d < 3; ++d) pb->V[d] = d < D ? V[d] : 0.0f;
-    return;
-  }
-  write_rec();
+  return r;
 }
 
 template <int D, int MODE>
-__global__ __launch_bounds__(kSweepBlock) void k_sweep(
-    const float* __restrict__ out_abs, int np_out,
-    const float* __restrict__ in_off, const float* __restrict__ in_A, const TileRec* __restrict__ in_tile,
-    int ntiles_in, int count_in, int nsplit, const int* __restrict__ hint,
-    void* __restrict__ part, double* __restrict__ part_ref, const Ctrl* __restrict__ ctrl, double eps_arg, int kofs,
-    int row_sweep, unsigned* __restrict__ tile_count) {
-  // blockIdx.x is the split and blockIdx.y the output block: consecutive
-  // workgroups go to consecutive XCDs, so the splits of one output block
-  // spread over all XCDs (a heavy output region does not load one XCD) and
-  // each XCD reads the input tiles of only splits / 8 splits (its L2 holds
-  // just those)
+__device__ __forceinline__ SplitSum sweep_split(const SweepIn& in, const SweepOut<D>& o, int split, int nsplit,
+                                                double M, int J, unsigned long long cand) {
+  if constexpr (MODE == kSweepPlain && D > 1) return sweep_split_mfma<D>(in, o, split, nsplit, M, J, cand);
+  else return sweep_split_valu<D, MODE>(in, o, split, nsplit, M, J, cand);
+}
+
+// A split's record: the shift relative to the output's reference in float32,
+// the sums rescaled by that rounding so that the record is exact.
+template <typename Rec>
+__device__ __forceinline__ Rec make_rec(const SplitSum& r, double Rref) {
+  float dM = -INFINITY, fix = 1.0f;
+  if (r.M > -INFINITY) {
+    const double dd = r.M - Rref;
+    dM = (float)dd;
+    fix = fast_exp2((float)(dd - (double)dM));
+  }
+  if constexpr (sizeof(Rec) == sizeof(PartialCert)) return Rec{dM, r.S * fix, r.N * fix, r.J};
+  else return Rec{dM, r.S * fix, r.J};
+}
+
+template <int MODE>
+struct RecOf { typedef PartialRec type; };
+template <>
+struct RecOf<kSweepCert> { typedef PartialCert type; };
+
+constexpr int kSweepWaves = 5;  // wavefronts per SIMD the sweeps' registers are held to
+
+// One block of kSweepBlock outputs (bx) against one split of the input tiles,
+// its records written to memory for k_finish.
+template <int D, int MODE>
+__device__ __forceinline__ void sweep_block(const SideDev& out, const SideDev& ins, int nsplit, const Partials& part,
+                                            const Ctrl* ctrl, double kap2_arg, int kofs, int bx, int split,
+                                            bool row_sweep, unsigned* __restrict__ tile_count, int slot) {
+  constexpr bool BARY = MODE == kSweepBary;
+  const SweepIn in = sweep_in(ins);
+  const int np_out = out.np;
+  const int p = bx * kSweepBlock + threadIdx.x;
+  const int lane = (int)(threadIdx.x & (kTile - 1));
+  const int nt = split_tiles(in.ntiles, split, nsplit);
+  // everything that depends on the arguments alone is requested first: a
+  // wavefront's start is round trips (these, then the warm start's gather)
+  float P[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) P[d] = ((gfloat*)out.abs)[(size_t)d * np_out + p];
+  const int j_hint = ((gint*)out.hint)[p];
+  // (clamped to a valid tile, also for an empty split)
+  const TileVals<D> first =
+      load_tile<D>(in.tile + min(split + max(min(lane, nt - 1), 0) * nsplit, in.ntiles - 1));
+  const CtrlVals cv = load_ctrl(ctrl, kofs);
+  const double kap2 = kap2_arg > 0.0 ? kap2_arg : row_sweep ? kap2_row(cv) : kap2_col(cv);
+  // (past the last tile: padding, copies of a point of the last tile)
+  const int tile = __builtin_amdgcn_readfirstlane(min(p / kTile, out.ntiles - 1));
+  const SweepOut<D> o = sweep_out<D>(P, (gtile*)out.tile + tile, kap2, ins.tskip);
+  double M;
+  int J;
+  warm_start<D>(in, o, j_hint, M, J);
+  const double cub = coarse_of<D>(first, o);
+  // the records' reference: the warm start's exponent (the same in every
+  // split), 0 without one; split 0 stores it for the merge
+  const double Rref = M > -INFINITY ? M : 0.0;
+  if (!BARY && split == 0) part.ref[p] = Rref;
+  const double gate = gate_min(M - o.tskip);  // a reduction over the wavefront: not under a lane's condition
+  const unsigned long long cand = __ballot(lane < nt && !(cub < gate));
+  const SplitSum r = sweep_split<D, MODE>(in, o, split, nsplit, M, J, cand);
+  if (tile_count && lane == 0) tile_count[slot] = (unsigned)r.evaluated;
+  if constexpr (BARY) {
+    PartialBary* pb = reinterpret_cast<PartialBary*>(part.rec) + (size_t)split * np_out + p;
+    pb->M = r.M;
+    pb->S = r.S;
+    for (int d = 0; d < 3; ++d) pb->V[d] = r.V[d];
+  } else {
+    typedef typename RecOf<MODE>::type Rec;
+    reinterpret_cast<Rec*>(part.rec)[(size_t)split * np_out + p] = make_rec<Rec>(r, Rref);
+  }
+}
+
+template <int D, int MODE>
+__global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSweepWaves))) void k_sweep(
+    LaunchCtx c, int transpose, int nsplit, double kap2_arg, int kofs) {
+  // blockIdx.x is the split and blockIdx.y the output block:
+  // consecutive workgroups go to consecutive XCDs, so the splits of one output
+  // block spread over all XCDs (a heavy output region does not load one XCD)
+  // and each XCD reads the input tiles of only part of the splits (its L2
+  // holds just those)
   const int slot = (blockIdx.y * gridDim.x + blockIdx.x) * (kSweepBlock / kTile) + threadIdx.x / kTile;
-  sweep_block<D, MODE>((gfloat*)out_abs, np_out, (gfloat*)in_off, (gfloat*)in_A, (gtile*)in_tile, ntiles_in,
-                       count_in, nsplit, hint, part, part_ref, (gctrl*)ctrl, eps_arg, kofs, blockIdx.y, blockIdx.x,
-                       row_sweep != 0, tile_count, slot);
+  sweep_block<D, MODE>(transpose ? c.cols : c.rows, transpose ? c.rows : c.cols, nsplit, c.part, c.ctrl,
+                       kap2_arg, kofs, blockIdx.y, blockIdx.x, transpose == 0, c.tile_count, slot);
 }
 
 // Batched sweep: block i runs work item i = (problem, block of outputs, split)
 // of a list over several problems; the arithmetic per item is the same as in
 // the single-problem launch.
 template <int D, int MODE>
-__global__ __launch_bounds__(kSweepBlock) void k_sweep_batch(const BatchItem* __restrict__ items,
-                                                        const LaunchCtx* __restrict__ descs, int transpose,
-                                                        int kofs) {
+__global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSweepWaves))) void k_sweep_batch(
+    const BatchItem* __restrict__ items, const LaunchCtx* __restrict__ descs, int transpose, int kofs) {
   const BatchItem it = items[blockIdx.x];
   const LaunchCtx& c = descs[it.prob];
-  const SideDev& out = transpose ? c.cols : c.rows;
-  const SideDev& in = transpose ? c.rows : c.cols;
-  const int splits = transpose ? c.splits_col : c.splits_row;
-  sweep_block<D, MODE>((gfloat*)out.abs, out.np, (gfloat*)in.off, (gfloat*)in.A, (gtile*)in.tile, in.ntiles,
-                       in.count, splits, out.hint, c.part.rec, c.part.ref, (gctrl*)c.ctrl, -1.0, kofs, it.blk, it.split,
+  sweep_block<D, MODE>(transpose ? c.cols : c.rows, transpose ? c.rows : c.cols,
+                       transpose ? c.splits_col : c.splits_row, c.part, c.ctrl, -1.0, kofs, it.blk, it.split,
                        transpose == 0, nullptr, 0);
 }
 
@@ -536,14 +788,16 @@ struct Merged {
   int J;        // input slot of the exact maximum of the winning split, or -1
 };
 
-template <typename Rec>
-__device__ __forceinline__ float rec_N(const Rec& q) { return 0.0f; }
-template <>
-__device__ __forceinline__ float rec_N<PartialCert>(const PartialCert& q) { return q.N; }
+// One split's record as the merge reads it.
+struct SplitRec {
+  float dM, S, N;
+  int J;
+};
+__device__ __forceinline__ SplitRec split_rec(const PartialRec& q) { return SplitRec{q.dM, q.S, 0.0f, q.J}; }
+__device__ __forceinline__ SplitRec split_rec(const PartialCert& q) { return SplitRec{q.dM, q.S, q.N, q.J}; }
 
-template <typename Rec>
-__device__ __forceinline__ Merged merge_splits_t(const Rec* __restrict__ part, const double* __restrict__ ref,
-                                                 int splits, int np, int p) {
+template <bool CERT, typename Load>
+__device__ __forceinline__ Merged merge_splits_t(Load load, double R, int splits) {
   // The epilogue runs few waves, so its time is the number of memory round
   // trips: one pass over the split records, G of them requested together.
   // Past the last split the index is clamped to a valid record and its shift
@@ -554,15 +808,14 @@ __device__ __forceinline__ Merged merge_splits_t(const Rec* __restrict__ part, c
   // if the batch holds a larger one (the running sums are rescaled).  Shifts
   // are relative to the output's reference R.
   constexpr int G = 16;
-  const double R = ref[p];
   float mx = -INFINITY;
   double S = 0.0, N = 0.0;
   int J = -1;
   auto batch = [&](int s0) {
-    Rec q[G];
+    SplitRec q[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      q[g] = part[(size_t)min(s0 + g, splits - 1) * np + p];
+      q[g] = load(min(s0 + g, splits - 1));
       q[g].dM += (s0 + g < splits) ? 0.0f : -INFINITY;
     }
     float bm = -INFINITY;
@@ -577,7 +830,7 @@ __device__ __forceinline__ Merged merge_splits_t(const Rec* __restrict__ part, c
       // shifts of one output differ by little: the weight is a hardware float32 exp2
       const double sc = mx == -INFINITY ? 0.0 : (double)fast_exp2(mx - bm);
       S *= sc;
-      N *= sc;
+      if (CERT) N *= sc;
       mx = bm;
       J = bj;
     }
@@ -586,7 +839,7 @@ __device__ __forceinline__ Merged merge_splits_t(const Rec* __restrict__ part, c
     for (int g = 0; g < G; ++g) {
       const double w = (double)fast_exp2(q[g].dM - mx);  // 0 for an empty or masked split
       S += w * (double)q[g].S;
-      N += w * (double)rec_N(q[g]);
+      if (CERT) N += w * (double)q[g].N;
     }
   };
   // the first batch outside the loop: at a loop header the wait counts are
@@ -603,8 +856,13 @@ __device__ __forceinline__ Merged merge_splits_t(const Rec* __restrict__ part, c
 }
 
 __device__ __forceinline__ Merged merge_splits(const Partials& pt, bool cert, int splits, int np, int p) {
-  if (cert) return merge_splits_t(reinterpret_cast<const PartialCert*>(pt.rec), pt.ref, splits, np, p);
-  return merge_splits_t(reinterpret_cast<const PartialRec*>(pt.rec), pt.ref, splits, np, p);
+  const double R = pt.ref[p];
+  if (cert) {
+    const PartialCert* rec = reinterpret_cast<const PartialCert*>(pt.rec) + p;
+    return merge_splits_t<true>([=](int s) { return split_rec(rec[(size_t)s * np]); }, R, splits);
+  }
+  const PartialRec* rec = reinterpret_cast<const PartialRec*>(pt.rec) + p;
+  return merge_splits_t<false>([=](int s) { return split_rec(rec[(size_t)s * np]); }, R, splits);
 }
 
 // Packs the weights w of one tile for the sweeps: a least-squares plane
@@ -614,43 +872,60 @@ __device__ __forceinline__ Merged merge_splits(const Partials& pt, bool cert, in
 // into an upper bound of its exponents), and per point
 // A_p = w2_p - alpha - gamma . b_p - kappa2 |b_p|^2 in float32 (-inf on padding
 // or for w = -inf), the part of the exponent that does not depend on the
-// output.  The record also holds the tile maximum of w2 - kappa2 |b|^2
-// (float64; -inf when the tile has no mass).  Called by whole wavefronts (one
-// tile each).
+// output; alpha is -inf when the tile has no mass.  Called by whole wavefronts
+// (one tile each).
 // Offsets of point p from its tile centre (0 past the real points); the
 // epilogues request them before they wait for the split records.
-// Three loads at clamped (valid) addresses whatever dim and p are, zeroed by a
-// multiplication (offsets are finite) rather than a select, so that every
-// loaded value is used and the loads issue together.
-__device__ __forceinline__ void load_offsets(const SideDev& sd, int dim, int p, float bo[3]) {
+// Loads at clamped (valid) addresses whatever p is, zeroed by a multiplication
+// (offsets are finite) rather than a select, so that every loaded value is
+// used and the loads issue together.
+template <int D>
+struct Offsets {
+  float b[D];
+};
+template <int D>
+__device__ __forceinline__ Offsets<D> load_offsets(const SideDev& sd, int p) {
   const int t = min(p, sd.count - 1) / kTile, q = p % kTile;
-  const float* base = sd.off + (size_t)t * dim * kTile + q;
+  const float* base = sd.off + (size_t)t * D * kTile + q;
+  Offsets<D> o;
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const float v = base[(size_t)min(d, dim - 1) * kTile];
-    bo[d] = v * ((p < sd.count && d < dim) ? 1.0f : 0.0f);
-  }
+  for (int d = 0; d < D; ++d) o.b[d] = base[(size_t)d * kTile] * (p < sd.count ? 1.0f : 0.0f);
+  return o;
+}
+
+// Geometry of the tile that the wavefront's points p belong to.
+template <int D>
+struct Geom {
+  double mb[D], cinv[6], cnt;
+};
+template <int D>
+__device__ __forceinline__ Geom<D> load_geom(const SideDev& sd, int p) {
+  const TileGeom* t = sd.geom + __builtin_amdgcn_readfirstlane(min(p / kTile, sd.ntiles - 1));
+  Geom<D> g;
+#pragma unroll
+  for (int d = 0; d < D; ++d) g.mb[d] = t->mb[d];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) g.cinv[i] = t->cinv[i];
+  g.cnt = t->cnt;
+  return g;
 }
 
 template <int D>
-__device__ __forceinline__ void pack_weight_d(const SideDev& sd, int p, double w, double kap2, const float bo[3]) {
+__device__ __forceinline__ void pack_weight_d(const SideDev& sd, const Geom<D>& g, int p, double w, double kap2,
+                                              const Offsets<D>& bo) {
   constexpr int dim = D;
   const bool live = p < sd.count && w > -INFINITY;
   const int t = p / kTile;
-  double A = -INFINITY, w2 = 0.0;
+  double w2 = 0.0;
   double b[D];
   float n2 = 0.0f;
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    b[d] = (double)bo[d];
-    n2 = fmaf(bo[d], bo[d], n2);
+    b[d] = (double)bo.b[d];
+    n2 = fmaf(bo.b[d], bo.b[d], n2);
   }
-  if (live) {
-    w2 = kLog2eD * w;
-    A = w2 - kap2 * (double)n2;
-  }
+  if (live) w2 = kLog2eD * w;
   if (p >= sd.ntiles * kTile) return;
-  const double m = wave_max(A);
   double gam[3] = {0.0, 0.0, 0.0}, alpha = -INFINITY;
   // least-squares plane through the live points of the tile (centred sums).
   // When the live points are the tile's real points (every weight finite, as
@@ -661,14 +936,13 @@ __device__ __forceinline__ void pack_weight_d(const SideDev& sd, int p, double w
   const int nreal = min(kTile, sd.count - t * kTile);
   const unsigned long long real_mask = nreal >= kTile ? ~0ull : ((1ull << nreal) - 1ull);
   if (__ballot(live) == real_mask) {
-    const TileGeom* g = sd.geom + t;
     const double wl = live ? w2 : 0.0;
     double v[D + 1];
     v[0] = wl;
 #pragma unroll
-    for (int d = 0; d < D; ++d) v[d + 1] = live ? (b[d] - g->mb[d]) * wl : 0.0;
+    for (int d = 0; d < D; ++d) v[d + 1] = live ? (b[d] - g.mb[d]) * wl : 0.0;
     wave_sum_n<D + 1>(v);
-    const double mw = v[0] / g->cnt;
+    const double mw = nreal == kTile ? v[0] * (1.0 / kTile) : v[0] / g.cnt;
     // symmetric inverse stored as xx, xy, xz, yy, yz, zz
     constexpr int kSym[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
     alpha = mw;
@@ -676,9 +950,9 @@ __device__ __forceinline__ void pack_weight_d(const SideDev& sd, int p, double w
     for (int d = 0; d < D; ++d) {
       double s = 0.0;
 #pragma unroll
-      for (int e = 0; e < D; ++e) s = fma(g->cinv[kSym[d][e]], v[e + 1], s);
+      for (int e = 0; e < D; ++e) s = fma(g.cinv[kSym[d][e]], v[e + 1], s);
       gam[d] = (double)(float)s;  // the sweep reads gamma as float32
-      alpha -= gam[d] * g->mb[d];
+      alpha -= gam[d] * g.mb[d];
     }
   } else {
     const double one = live ? 1.0 : 0.0;
@@ -739,24 +1013,16 @@ __device__ __forceinline__ void pack_weight_d(const SideDev& sd, int p, double w
   const double rho = wave_max(fabs(res));
   if ((threadIdx.x & (kTile - 1)) == 0) {
     TileRec& tr = sd.tile[t];
-    tr.amax = m;
     tr.alpha = alpha;
     for (int d = 0; d < 3; ++d) tr.gam[d] = (float)gam[d];
     tr.rho = (float)(rho * (1.0 + 1e-6)) + 1e-3f;  // rounded up: the bound must hold
   }
 }
 
-__device__ __forceinline__ void pack_weight(const SideDev& sd, int dim, int p, double w, double kap2,
-                                            const float bo[3]) {
-  if (dim == 1) pack_weight_d<1>(sd, p, w, kap2, bo);
-  else if (dim == 2) pack_weight_d<2>(sd, p, w, kap2, bo);
-  else pack_weight_d<3>(sd, p, w, kap2, bo);
-}
-
 __device__ __forceinline__ void pack_weight(const SideDev& sd, int dim, int p, double w, double kap2) {
-  float bo[3];
-  load_offsets(sd, dim, p, bo);
-  pack_weight(sd, dim, p, w, kap2, bo);
+  if (dim == 1) pack_weight_d<1>(sd, load_geom<1>(sd, p), p, w, kap2, load_offsets<1>(sd, p));
+  else if (dim == 2) pack_weight_d<2>(sd, load_geom<2>(sd, p), p, w, kap2, load_offsets<2>(sd, p));
+  else pack_weight_d<3>(sd, load_geom<3>(sd, p), p, w, kap2, load_offsets<3>(sd, p));
 }
 
 // Merge of the barycentric partials of output p: shift, shifted sum and the
@@ -785,49 +1051,51 @@ __device__ __forceinline__ MergedBary merge_bary(const void* __restrict__ part, 
   return r;
 }
 
-// Merge + epilogue of one tile (bx) of 64 outputs; nblocks = tiles of the
-// output side (the column epilogue's last block advances k).
-__device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, int kind, int splits,
-                                             double eps_arg, double* __restrict__ lse_out, int bx, int kofs) {
+// What the epilogues read that does not depend on the merge.
+template <int D>
+struct FinishPre {
+  CtrlVals cv;
+  Offsets<D> bo;                   // offsets the packing needs
+  double lm, s, t0, t1;            // log marginal and dual state of output p
+  Geom<D> geom;                    // of the tile being packed
+};
+
+// An epilogue runs one wavefront per output tile, so its time is the number
+// of memory round trips: these loads are issued before the split records are
+// waited for.  Unconditional (p < np, and every array read here holds np
+// entries of the output side): a load under a branch is waited for there.
+template <int D>
+__device__ __forceinline__ FinishPre<D> finish_loads(const LaunchCtx& c, int transpose, int p, int kofs) {
   const SideDev& out = transpose ? c.cols : c.rows;
-  const int p = bx * kTile + threadIdx.x;
-  const int np = out.np;
-  if (p >= np) return;
-  const bool real = p < out.count;
-  if (kind == kFinishPlanRow) {
-    // state plan: (X 1)_i = alpha_i sum_j K_ij beta_j, barycentre sum_j X_ij y_j / (X 1)_i
-    const MergedBary mb = merge_bary(c.part.rec, splits, np, p);
-    if (real) {
-      c.plan_row[p] = exp(c.st.la[p] + mb.lse);
-      if (lse_out) {
-        const int i = out.perm[p];
-        for (int d = 0; d < c.dim; ++d) lse_out[(size_t)i * c.dim + d] = c.origin[d] + mb.V[d];
-      }
-    }
-    return;
-  }
-  const bool cert = (kind == kFinishColCert || kind == kFinishCertOnly);
-  const bool iter_kind = kind == kFinishRow || kind == kFinishCol || kind == kFinishColCert;
-  // An epilogue runs one wavefront per output tile, so its time is the number
-  // of memory round trips: what the iteration's epilogues read that does not
-  // depend on the merge (control block, marginal, dual state, the offsets the
-  // packing needs) is requested before the split records are waited for.
-  // Unconditional loads (p < np, and every array read here holds np entries
-  // of the output side): a load under a branch is waited for there.
-  const Ctrl cv = *c.ctrl;
-  float bo[3];
-  load_offsets(out, c.dim, p, bo);
+  FinishPre<D> f;
+  f.cv = load_ctrl(c.ctrl, kofs);
+  f.bo = load_offsets<D>(out, p);
   const double* s_arr = transpose ? c.st.lb1 : c.st.la;
   const double* t0_arr = transpose ? c.st.lt[0] : c.st.la;
   const double* t1_arr = transpose ? c.st.lt[1] : c.st.la;
-  const double pre_lm = out.logmarg[p], pre_s = s_arr[p], pre_t0 = t0_arr[p], pre_t1 = t1_arr[p];
-  // the sweeps that gathered cost-weighted sums wrote certificate records
-  const bool cert_rec = kind == kFinishColCert || kind == kFinishCertOnly || kind == kFinishRound3;
-  const Merged mg = merge_splits(c.part, cert_rec, splits, np, p);
+  f.lm = out.logmarg[p];
+  f.s = s_arr[p];
+  f.t0 = t0_arr[p];
+  f.t1 = t1_arr[p];
+  f.geom = load_geom<D>(out, p);
+  return f;
+}
+
+// Epilogue of output p from its merged sums (whole wavefronts, one output
+// tile each).
+template <int D>
+__device__ __forceinline__ void finish_out(const LaunchCtx& c, int transpose, int kind,
+                                           double* __restrict__ lse_out, int p, const Merged& mg,
+                                           const FinishPre<D>& pre) {
+  const SideDev& out = transpose ? c.cols : c.rows;
+  const bool real = p < out.count;
+  const bool cert = (kind == kFinishColCert || kind == kFinishCertOnly);
+  const bool iter_kind = kind == kFinishRow || kind == kFinishCol || kind == kFinishColCert;
+  const double pre_lm = pre.lm, pre_s = pre.s, pre_t0 = pre.t0, pre_t1 = pre.t1;
   // the warm start of the next sweep of this side: only the iteration's own sweeps set it
   if (real && iter_kind && mg.J >= 0) out.hint[p] = mg.J;
-  const Ctrl* ctrl = &cv;
-  const long long k = ctrl->k + kofs;  // this iteration: the block's first plus the offset
+  const CtrlVals* ctrl = &pre.cv;
+  const long long k = ctrl->k;  // this iteration: the block's first plus the offset
   const double lam = ctrl->lam;
 
   if (kind == kFinishLse) {
@@ -882,8 +1150,7 @@ __device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, 
   if (kind == kFinishRow) {
     // row update of Algorithm 1: the unrelaxed row scaling normalises the rows to r; the
     // relaxed one mixes it with the previous relaxed scaling, weight lambda on the new one
-    const double eps = eps_of(ctrl, eps_arg, kofs);
-    const double kap2 = kLog2eD * ctrl->scale / eps;
+    const double kap2 = kap2_col(*ctrl);
     double colw = 0.0;
     if (real) {
       const double lah = pre_lm - mg.lse;
@@ -902,7 +1169,7 @@ __device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, 
     }
     // weights of the column sweep of the same iteration: log alpha-hat (the
     // debiased variant: its row scaling a^k)
-    pack_weight(c.rows, c.dim, p, colw, kap2, bo);
+    pack_weight_d<D>(c.rows, pre.geom, p, colw, kap2, pre.bo);
     return;
   }
   // column epilogue (plain or certificate)
@@ -925,15 +1192,42 @@ __device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, 
     lt_next = (ctrl->variant & kVarNoMomentum) ? lb : lb + (lb - lb1) / lam;
     c.st.lt[nxt][p] = lt_next;
   }
-  const double eps1 = eps_row_of(ctrl, -1.0, kofs + 1);
-  const double kap2n = kLog2eD * ctrl->scale / eps1;
-  pack_weight(c.cols, c.dim, p, lt_next, kap2n, bo);
+  pack_weight_d<D>(c.cols, pre.geom, p, lt_next, kap2_row(*ctrl, 1), pre.bo);
+}
 
+// Merge of the records in memory + epilogue of one tile (bx) of 64 outputs.
+template <int D>
+__device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, int kind, int splits,
+                                             double* __restrict__ lse_out, int bx, int kofs) {
+  const SideDev& out = transpose ? c.cols : c.rows;
+  const int p = bx * kTile + threadIdx.x;
+  const int np = out.np;
+  if (p >= np) return;
+  if (kind == kFinishPlanRow) {
+    // state plan: (X 1)_i = alpha_i sum_j K_ij beta_j, barycentre sum_j X_ij y_j / (X 1)_i
+    const MergedBary mb = merge_bary(c.part.rec, splits, np, p);
+    if (p < out.count) {
+      c.plan_row[p] = exp(c.st.la[p] + mb.lse);
+      if (lse_out) {
+        const int i = out.perm[p];
+#pragma unroll
+        for (int d = 0; d < D; ++d) lse_out[(size_t)i * D + d] = c.origin[d] + mb.V[d];
+      }
+    }
+    return;
+  }
+  const FinishPre<D> pre = finish_loads<D>(c, transpose, p, kofs);
+  // the sweeps that gathered cost-weighted sums wrote certificate records
+  const bool cert_rec = kind == kFinishColCert || kind == kFinishCertOnly || kind == kFinishRound3;
+  const Merged mg = merge_splits(c.part, cert_rec, splits, np, p);
+  finish_out<D>(c, transpose, kind, lse_out, p, mg, pre);
 }
 
 __global__ __launch_bounds__(kTile) void k_finish(LaunchCtx c, int transpose, int kind, int splits,
-                                                  double eps_arg, double* __restrict__ lse_out, int kofs) {
-  finish_block(c, transpose, kind, splits, eps_arg, lse_out, blockIdx.x, kofs);
+                                                  double* __restrict__ lse_out, int kofs) {
+  if (c.dim == 1) finish_block<1>(c, transpose, kind, splits, lse_out, blockIdx.x, kofs);
+  else if (c.dim == 2) finish_block<2>(c, transpose, kind, splits, lse_out, blockIdx.x, kofs);
+  else finish_block<3>(c, transpose, kind, splits, lse_out, blockIdx.x, kofs);
 }
 
 // Advances the iteration counter by n after a block of n iterations (kernels of
@@ -954,7 +1248,10 @@ __global__ __launch_bounds__(kTile) void k_finish_batch(const BatchItem* __restr
                                                         int kind, int kofs) {
   const BatchItem it = items[blockIdx.x];
   const LaunchCtx& c = descs[it.prob];
-  finish_block(c, transpose, kind, transpose ? c.splits_col : c.splits_row, -1.0, nullptr, it.blk, kofs);
+  const int splits = transpose ? c.splits_col : c.splits_row;
+  if (c.dim == 1) finish_block<1>(c, transpose, kind, splits, nullptr, it.blk, kofs);
+  else if (c.dim == 2) finish_block<2>(c, transpose, kind, splits, nullptr, it.blk, kofs);
+  else finish_block<3>(c, transpose, kind, splits, nullptr, it.blk, kofs);
 }
 
 // lt and A_C of iteration k from the stored log beta^{k-1}, log beta^{k-2}.
@@ -970,7 +1267,7 @@ __global__ __launch_bounds__(kBlock) void k_prologue(LaunchCtx c) {
     lt = (c.ctrl->variant & kVarNoMomentum) ? lb1 : lb1 + (lb1 - lb2) / lam;
     c.st.lt[k & 1][p] = lt;
   }
-  const double kap2 = kLog2eD * c.ctrl->scale / eps_row_of(c.ctrl, -1.0, 0);
+  const double kap2 = kap2_row(load_ctrl(c.ctrl, 0));
   pack_weight(c.cols, c.dim, p, lt, kap2);
 }
 
@@ -1072,7 +1369,7 @@ __global__ __launch_bounds__(kBlock) void k_repair_pack(LaunchCtx c) {
     const double cj = c.cols.marg[p];
     if (s > cj) w = c.st.lt[k & 1][p] + log1p(-cj / s);
   }
-  const double kap2 = kLog2eD * c.ctrl->scale / eps_row_of(c.ctrl, -1.0, -1);
+  const double kap2 = kap2_row(load_ctrl(c.ctrl, -1));
   pack_weight(c.cols, c.dim, p, w, kap2);
 }
 
@@ -1500,21 +1797,21 @@ int choose_splits(int np_out, int ntiles_in) {
   return (ntiles_in + tps - 1) / tps;  // splits that own at least one tile
 }
 
+static double kap2_arg_of(const LaunchCtx& c, double eps_arg) {
+  return eps_arg > 0.0 ? kLog2eD * c.scale / eps_arg : -1.0;
+}
+
 hipError_t launch_sweep(const LaunchCtx& c, bool transpose, bool cert, int splits, double eps_arg, int kofs) {
   const SideDev& out = transpose ? c.cols : c.rows;
-  const SideDev& in = transpose ? c.rows : c.cols;
   dim3 grid(splits, out.np / kSweepBlock);  // x: split, y: output block (see k_sweep)
-#define BDRS_SWEEP(DD, CC)                                                                             \
-  if (c.ev_start && c.ev_stop)                                                                         \
+  const double kap2 = kap2_arg_of(c, eps_arg);
+#define BDRS_SWEEP(DD, CC)                                                                                \
+  if (c.ev_start && c.ev_stop)                                                                            \
     hipExtLaunchKernelGGL((k_sweep<DD, CC>), grid, dim3(kSweepBlock), 0, c.stream, c.ev_start, c.ev_stop, \
-                          0u, (const float*)out.abs, (int)out.np, (const float*)in.off,                 \
-                          (const float*)in.A, (const TileRec*)in.tile, (int)in.ntiles, (int)in.count,   \
-                          (int)splits, (const int*)out.hint, (void*)c.part.rec, (double*)c.part.ref, (const Ctrl*)c.ctrl, \
-                          (double)eps_arg, (int)kofs, (int)(transpose ? 0 : 1), (unsigned*)c.tile_count);  \
-  else                                                                                                 \
-    hipLaunchKernelGGL((k_sweep<DD, CC>), grid, dim3(kSweepBlock), 0, c.stream, out.abs, out.np, in.off, \
-                       in.A, in.tile, in.ntiles, in.count, splits, out.hint,                               \
-                       c.part.rec, c.part.ref, c.ctrl, eps_arg, kofs, transpose ? 0 : 1, c.tile_count)
+                          0u, c, (int)(transpose ? 1 : 0), splits, kap2, kofs);                           \
+  else                                                                                                    \
+    hipLaunchKernelGGL((k_sweep<DD, CC>), grid, dim3(kSweepBlock), 0, c.stream, c, transpose ? 1 : 0, splits, \
+                       kap2, kofs)
   switch (c.dim * 2 + (cert ? 1 : 0)) {
     case 2: BDRS_SWEEP(1, kSweepPlain); break;
     case 3: BDRS_SWEEP(1, kSweepCert); break;
@@ -1530,13 +1827,10 @@ hipError_t launch_sweep(const LaunchCtx& c, bool transpose, bool cert, int split
 
 hipError_t launch_sweep_bary(const LaunchCtx& c, int splits, double eps) {
   const SideDev& out = c.rows;
-  const SideDev& in = c.cols;
   dim3 grid(splits, out.np / kSweepBlock);  // x: split, y: output block (see k_sweep)
-#define BDRS_SWEEP(DD)                                                                                  \
-  hipLaunchKernelGGL((k_sweep<DD, kSweepBary>), grid, dim3(kSweepBlock), 0, c.stream, out.abs, out.np,   \
-                     in.off, in.A, in.tile, in.ntiles, in.count, splits, out.hint, c.part.rec, c.part.ref, c.ctrl, eps, \
-                     0, 1, \
-                     c.tile_count)
+#define BDRS_SWEEP(DD) \
+  hipLaunchKernelGGL((k_sweep<DD, kSweepBary>), grid, dim3(kSweepBlock), 0, c.stream, c, 0, splits, \
+                     kap2_arg_of(c, eps), 0)
   switch (c.dim) {
     case 1: BDRS_SWEEP(1); break;
     case 2: BDRS_SWEEP(2); break;
@@ -1547,12 +1841,12 @@ hipError_t launch_sweep_bary(const LaunchCtx& c, int splits, double eps) {
   return hipGetLastError();
 }
 
-hipError_t launch_finish(const LaunchCtx& c, bool transpose, FinishKind kind, int splits, double eps_arg,
-                         double* lse_out, int kofs) {
+hipError_t launch_finish(const LaunchCtx& c, bool transpose, FinishKind kind, int splits, double* lse_out,
+                         int kofs) {
   // one wavefront per block (one tile of outputs), so the O(n) epilogue spreads over all CUs
   const SideDev& out = transpose ? c.cols : c.rows;
   hipLaunchKernelGGL(k_finish, dim3(out.ntiles), dim3(kTile), 0, c.stream, c, transpose ? 1 : 0,
-                     (int)kind, splits, eps_arg, lse_out, kofs);
+                     (int)kind, splits, lse_out, kofs);
   return hipGetLastError();
 }
 

@@ -46,6 +46,12 @@ double median_of(std::vector<float> v) {
   return v.size() % 2 ? (double)v[h] : 0.5 * ((double)v[h - 1] + (double)v[h]);
 }
 
+// One sweep with its epilogue, as an iteration launches it.
+hipError_t half(const LaunchCtx& c, bool transpose, FinishKind kind, int splits) {
+  const hipError_t e = launch_sweep(c, transpose, false, splits, -1.0, 0);
+  return e == hipSuccess ? launch_finish(c, transpose, kind, splits, nullptr, 0) : e;
+}
+
 int tiles_of(int count) { return (count + kTile - 1) / kTile; }
 
 }  // namespace
@@ -154,11 +160,9 @@ bdrs_status bdrs_autotune(const bdrs_params* p, int32_t rounds, bdrs_tune_entry*
       c.splits_row = sr;
       c.splits_col = sc;
       e = hipEventRecord(ev[3 * i], c.stream);
-      if (e == hipSuccess) e = launch_sweep(c, false, false, sr, -1.0, 0);
-      if (e == hipSuccess) e = launch_finish(c, false, kFinishRow, sr, -1.0, nullptr, 0);
+      if (e == hipSuccess) e = half(c, false, kFinishRow, sr);
       if (e == hipSuccess) e = hipEventRecord(ev[3 * i + 1], c.stream);
-      if (e == hipSuccess) e = launch_sweep(c, true, false, sc, -1.0, 0);
-      if (e == hipSuccess) e = launch_finish(c, true, kFinishCol, sc, -1.0, nullptr, 0);
+      if (e == hipSuccess) e = half(c, true, kFinishCol, sc);
       if (e == hipSuccess) e = hipEventRecord(ev[3 * i + 2], c.stream);
       if (e == hipSuccess) e = launch_advance(c.ctrl, 1, c.stream);
     }

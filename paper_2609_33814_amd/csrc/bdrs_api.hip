@@ -329,14 +329,13 @@ void build_side(const float* pts, const double* w, int count, int dim, const dou
 // skipped.  Every output's sum is at least 2^M (the term that set M is
 // summed), and the skipped terms add at most n 2^{M-T} <= 2^{M-30}: 1/64 of
 // float32's half-ulp, below the rounding of the float32 sum itself.
-double skip_depth(int n) { return std::min(64.0, 30.0 + std::ceil(std::log2((double)std::max(n, 1)))); }
+int skip_depth(int n) { return std::min(64, 30 + (int)std::ceil(std::log2((double)std::max(n, 1)))); }
 
 void fill_ctx(bdrs_solver s) {
   const Layout& L = s->L;
   char* base = (char*)s->prm.workspace;
   LaunchCtx& c = s->ctx;
   c.stream = (hipStream_t)s->prm.stream;
-  c.scale = s->prm.cost_scale;
   c.dim = s->prm.dim;
   c.splits_row = L.splits_row;
   c.splits_col = L.splits_col;
@@ -346,7 +345,6 @@ void fill_ctx(bdrs_solver s) {
     sd.count = sh.count;
     sd.ntiles = sh.ntiles;
     sd.np = sh.np;
-    sd.pad = 0;
     sd.tskip = skip_depth(sh.count);
     sd.abs = (float*)(base + abs);
     sd.off = (float*)(base + off);
@@ -709,9 +707,9 @@ hipError_t BatchEngine::enqueue(hipStream_t st) {
   for (int i = 0; i < iters_ && e == hipSuccess; ++i) {
     const bool cert = (i == iters_ - 1);
     e = launch_sweep_batch(rs, nrs_, descs, dim_, false, false, i, st);
-    if (e == hipSuccess) e = launch_finish_batch(rf, nrf_, descs, false, kFinishRow, i, st);
+    if (e == hipSuccess) e = launch_finish_batch(rf, nrf_, descs, dim_, kFinishRow, i, st);
     if (e == hipSuccess) e = launch_sweep_batch(cs, ncs_, descs, dim_, true, cert, i, st);
-    if (e == hipSuccess) e = launch_finish_batch(cf, ncf_, descs, true, cert ? kFinishColCert : kFinishCol, i, st);
+    if (e == hipSuccess) e = launch_finish_batch(cf, ncf_, descs, dim_, cert ? kFinishColCert : kFinishCol, i, st);
   }
   if (e == hipSuccess) e = launch_advance_batch(descs, (int)members_.size(), iters_, st);
   if (e == hipSuccess)

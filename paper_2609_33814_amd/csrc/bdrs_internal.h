@@ -70,7 +70,7 @@ struct SideDev {
   int count;       // real points
   int ntiles;      // ceil(count / 64)
   int np;          // ntiles * 64, padded to a multiple of 256 for the epilogues
-  int pad;
+  int tskip;       // depth T of the skip gate of a sweep with this side as input
   float* abs;      // [dim][np] coordinates relative to the common origin (SoA)
   float* off;      // [ntiles][dim][64] offsets from the tile centre
   float* A;        // [np] log2 weights of the next sweep that reads this side minus their
@@ -83,7 +83,6 @@ struct SideDev {
                    //      input point whose term is near the output's maximum, or -1
   double* marg;    // [np] marginal (r or c), 0 on padding
   double* logmarg; // [np] log marginal
-  double tskip;    // depth T of the skip gate of a sweep with this side as input
 };
 
 // Dual state (float64, tile order; O(m + n)).
@@ -161,7 +160,6 @@ enum FinishKind {
 
 struct LaunchCtx {
   hipStream_t stream;
-  double scale;    // cost scale s
   int dim;
   int splits_row, splits_col;  // input splits of the row / column sweep
   Ctrl* ctrl;
@@ -233,8 +231,8 @@ hipError_t launch_hints_in(const int* src, const int* perm_out, const int* iperm
 // Batched phases over the problems in `descs` (device array of LaunchCtx).
 hipError_t launch_sweep_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, int dim,
                               bool transpose, bool cert, int kofs, hipStream_t s);
-hipError_t launch_finish_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, bool transpose,
-                               FinishKind kind, int kofs, hipStream_t s);
+hipError_t launch_finish_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, int dim, FinishKind kind,
+                               int kofs, hipStream_t s);
 hipError_t launch_advance_batch(const LaunchCtx* descs, int count, int n, hipStream_t s);
 hipError_t launch_cert_batch(const BatchItem* items, int nitems, const int* probs, int nprobs,
                              const LaunchCtx* descs, double* records, hipStream_t s);

@@ -47,6 +47,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace bdrs {
 
@@ -77,13 +78,13 @@ __device__ __forceinline__ double fast_div(double a, double b) {
 typedef __attribute__((address_space(4))) const Ctrl cctrl;
 struct CtrlVals {
   double eta, lam, scale;
-  long long k;  // of this launch's iteration
+  long long k;  // first iteration of the block
   unsigned variant;
 };
-__device__ __forceinline__ CtrlVals load_ctrl(const Ctrl* c, int kofs) {
+__device__ __forceinline__ CtrlVals load_ctrl(const Ctrl* c) {
   cctrl* p = (cctrl*)c;
   CtrlVals v;
-  v.k = p->k + kofs;
+  v.k = p->k;
   v.variant = p->variant;
   v.eta = p->eta;
   v.lam = p->lam;
@@ -91,18 +92,25 @@ __device__ __forceinline__ CtrlVals load_ctrl(const Ctrl* c, int kofs) {
   return v;
 }
 
-// kappa2 = log2(e) s / eps of the column update of iteration k + ahead, at
-// eta_k = eta / (lambda k + 1).
-__device__ __forceinline__ double kap2_col(const CtrlVals& c, int ahead = 0) {
-  return fast_div(kLog2eD * c.scale, fast_div(c.eta, c.lam * (double)(c.k + ahead) + 1.0));
+// kappa2 = log2(e) s / eps at the temperature of the column update of iteration
+// c.k + ahead, eta_k = eta / (lambda k + 1), or (ROW) of its row update: the
+// same, or eta / k for the old kernel K^{.k} (at k = 0 one at which every cost
+// term vanishes).  No branches: they would hold back the loads after them.
+template <bool ROW>
+__device__ __forceinline__ double kap2_of(const CtrlVals& c, int ahead) {
+  const double k = (double)(c.k + ahead);
+  double den = c.lam * k + 1.0;
+  if (ROW) den = c.variant & kVarOldKernel ? (k >= 1.0 ? k : 1.0 / kFarTemperature) : den;
+  return fast_div(kLog2eD * c.scale, fast_div(c.eta, den));
 }
 
-// The same of the row update: eta_k, or eta / k for the old kernel K^{.k} (at
-// k = 0 a temperature at which every cost term vanishes).
-__device__ __forceinline__ double kap2_row(const CtrlVals& c, int ahead = 0) {
-  if (!(c.variant & kVarOldKernel)) return kap2_col(c, ahead);
-  const long long k = c.k + ahead;
-  return fast_div(kLog2eD * c.scale, k >= 1 ? fast_div(c.eta, (double)k) : c.eta * kFarTemperature);
+// The control block with the temperature of a sweep called with its own eps
+// (eps > 0): eta = eps and lambda = 0 give eps whatever k is.
+__device__ __forceinline__ CtrlVals with_eps(CtrlVals c, double eps, bool own) {
+  c.eta = own ? eps : c.eta;
+  c.lam = own ? 0.0 : c.lam;
+  c.variant = own ? 0u : c.variant;
+  return c;
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -267,19 +275,19 @@ struct SplitSum {
   int evaluated;  // input tiles this wavefront evaluated (the same on every lane)
 };
 
-// rec: the record of the outputs' own tile, whose box (widened against the
+// own: the record of the outputs' own tile, whose box (widened against the
 // rounding of its centre and radius) holds the wavefront's 64 points.
 template <int D>
-__device__ __forceinline__ SweepOut<D> sweep_out(const float (&P)[D], gtile* rec, double kap2, double tskip) {
+__device__ __forceinline__ SweepOut<D> sweep_out(const float (&P)[D], const TileVals<D>& own, double kap2,
+                                                 double tskip) {
   SweepOut<D> o;
   o.kap2d = kap2;
   o.kap2f = (float)kap2;
   o.inv2kap = (float)(0.5 * fast_rcp(kap2));
   o.tskip = tskip;
-  gfloat* fp = (gfloat*)rec;
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    const float ctr = fp[2 + d], half = fp[5 + d] * 1.000001f + fabsf(ctr) * 1e-6f;
+    const float ctr = own.ctr[d], half = own.rad[d] * 1.000001f + fabsf(ctr) * 1e-6f;
     o.P[d] = P[d];
     o.blo[d] = ctr - half;
     o.bhi[d] = ctr + half;
@@ -294,13 +302,10 @@ __device__ __forceinline__ double gate_min(double Mlo) {
   return (double)fmaf(-1e-6f, fabsf(m), m) - 1e-6;
 }
 
-// Tiles of split `split`: split, split + nsplit, ... (local index i is tile
-// split + i nsplit), so that each split samples the whole input cloud: late in
-// a solve only the tiles near an output block matter, and they spread over all
-// splits instead of crowding into one wavefront's work.
-__device__ __forceinline__ int split_tiles(int ntiles, int split, int nsplit) {
-  return split < ntiles ? (ntiles - 1 - split) / nsplit + 1 : 0;
-}
+// Split `split` of nsplit takes the tiles split, split + nsplit, ... (local
+// index i is tile split + i nsplit), so that each split samples the whole input
+// cloud: late in a solve only the tiles near an output block matter, and they
+// spread over all splits instead of crowding into one wavefront's work.
 
 // Coarse test of up to 64 tiles at once, lane l taking local tile c0 + l: an
 // upper bound of the exponents of the tile's points for every output of the
@@ -323,14 +328,13 @@ __device__ __forceinline__ double coarse_of(const TileVals<D>& t, const SweepOut
   return t.alpha + (double)fmaf(-o.kap2f, g2, w);
 }
 
-// Candidates among local tiles c0 ... c1-1 of a split, as a bit mask.
+// Candidates among the local tiles c0 ... c0+63 of a split, as a bit mask.
 template <int D>
 __device__ __forceinline__ unsigned long long coarse_mask(const SweepIn& in, const SweepOut<D>& o, double gate,
-                                                          int split, int nsplit, int c0, int c1) {
-  const int lane = (int)(threadIdx.x & (kTile - 1));
-  const int il = max(min(c0 + lane, c1 - 1), 0);
-  const double cub = coarse_of<D>(load_tile<D>(in.tile + min(split + il * nsplit, in.ntiles - 1)), o);
-  return __ballot(c0 + lane < c1 && !(cub < gate));
+                                                          int split, int nsplit, int c0) {
+  const int t = split + (c0 + (int)(threadIdx.x & (kTile - 1))) * nsplit;
+  const double cub = coarse_of<D>(load_tile<D>(in.tile + min(t, in.ntiles - 1)), o);
+  return __ballot(t < in.ntiles && !(cub < gate));
 }
 
 // Warm start: the exact exponent of one remembered input point is a lower
@@ -506,13 +510,11 @@ __device__ __forceinline__ SplitSum sweep_split_mfma(const SweepIn& in, const Sw
   const int lane = (int)(threadIdx.x & (kTile - 1));
   const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
   const int pt = (lane & ~6) | ((lane & 2) << 1) | ((lane & 4) >> 1);
-  const int nt = split_tiles(in.ntiles, split, nsplit);
   SplitSum r{M, 0.0f, 0.0f, {0.0f, 0.0f, 0.0f}, J, 0};
   double Mth = M + kThresh;      // the exact-max gate, updated with M
   double Mlo = M - o.tskip;      // the skip gate, updated with M
-  for (int c0 = 0; c0 < nt; c0 += kTile) {
-    const int c1 = min(c0 + kTile, nt);
-    if (c0 != 0) cand = coarse_mask<D>(in, o, gate_min(Mlo), split, nsplit, c0, c1);
+  for (int c0 = 0; split + c0 * nsplit < in.ntiles; c0 += kTile) {
+    if (c0 != 0) cand = coarse_mask<D>(in, o, gate_min(Mlo), split, nsplit, c0);
     if (!cand) continue;
     int t = split + (c0 + __builtin_ctzll(cand)) * nsplit;
     TileVals<D> cur = load_tile<D>(in.tile + t);
@@ -569,14 +571,12 @@ __device__ __forceinline__ SplitSum sweep_split_valu(const SweepIn& in, const Sw
   constexpr bool CERT = MODE == kSweepCert;
   constexpr bool BARY = MODE == kSweepBary;
   const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
-  const int nt = split_tiles(in.ntiles, split, nsplit);
   SplitSum r{M, 0.0f, 0.0f, {0.0f, 0.0f, 0.0f}, J, 0};
   double Mth = M + kThresh;      // the exact-max gate, updated with M
   double Mlo = M - o.tskip;      // the skip gate, updated with M
   Group<D> grp;
-  for (int c0 = 0; c0 < nt; c0 += kTile) {
-    const int c1 = min(c0 + kTile, nt);
-    if (c0 != 0) cand = coarse_mask<D>(in, o, gate_min(Mlo), split, nsplit, c0, c1);
+  for (int c0 = 0; split + c0 * nsplit < in.ntiles; c0 += kTile) {
+    if (c0 != 0) cand = coarse_mask<D>(in, o, gate_min(Mlo), split, nsplit, c0);
     if (cand) {
       const int tf = split + (c0 + __builtin_ctzll(cand)) * nsplit;
       grp = load_group<D>(in.off + (size_t)tf * D * kTile, in.A + (size_t)tf * kTile + lane0, 0);
@@ -705,30 +705,36 @@ constexpr int kSweepWaves = 5;  // wavefronts per SIMD the sweeps' registers are
 
 // One block of kSweepBlock outputs (bx) against one split of the input tiles,
 // its records written to memory for k_finish.
-template <int D, int MODE>
-__device__ __forceinline__ void sweep_block(const SideDev& out, const SideDev& ins, int nsplit, const Partials& part,
-                                            const Ctrl* ctrl, double kap2_arg, int kofs, int bx, int split,
-                                            bool row_sweep, unsigned* __restrict__ tile_count, int slot) {
+template <int D, int MODE, bool ROW>
+__device__ __forceinline__ void sweep_block(const LaunchCtx& c, int nsplit, double eps, int own, int kofs, int bx,
+                                            int split, unsigned* __restrict__ tile_count, int slot) {
   constexpr bool BARY = MODE == kSweepBary;
+  const SideDev& out = ROW ? c.rows : c.cols;
+  const SideDev& ins = ROW ? c.cols : c.rows;
   const SweepIn in = sweep_in(ins);
+  const Partials part = c.part;
+  // arguments that are used late are loaded with the others all the same: the
+  // compiler would load them where they are used, a scalar round trip each
+  asm volatile("" ::"s"(ins.tskip), "s"(part.ref), "s"(part.rec), "s"(tile_count), "s"(in.off), "s"(in.A), "s"(c.ctrl));
   const int np_out = out.np;
   const int p = bx * kSweepBlock + threadIdx.x;
   const int lane = (int)(threadIdx.x & (kTile - 1));
-  const int nt = split_tiles(in.ntiles, split, nsplit);
   // everything that depends on the arguments alone is requested first: a
   // wavefront's start is round trips (these, then the warm start's gather)
   float P[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) P[d] = ((gfloat*)out.abs)[(size_t)d * np_out + p];
   const int j_hint = ((gint*)out.hint)[p];
-  // (clamped to a valid tile, also for an empty split)
-  const TileVals<D> first =
-      load_tile<D>(in.tile + min(split + max(min(lane, nt - 1), 0) * nsplit, in.ntiles - 1));
-  const CtrlVals cv = load_ctrl(ctrl, kofs);
-  const double kap2 = kap2_arg > 0.0 ? kap2_arg : row_sweep ? kap2_row(cv) : kap2_col(cv);
+  const int t = split + lane * nsplit;
+  const TileVals<D> first = load_tile<D>(in.tile + min(t, in.ntiles - 1));
   // (past the last tile: padding, copies of a point of the last tile)
-  const int tile = __builtin_amdgcn_readfirstlane(min(p / kTile, out.ntiles - 1));
-  const SweepOut<D> o = sweep_out<D>(P, (gtile*)out.tile + tile, kap2, ins.tskip);
+  const int tile = min(bx * (kSweepBlock / kTile) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kTile)),
+                       out.ntiles - 1);
+  const TileVals<D> own_tile = load_tile<D>((gtile*)out.tile + tile);
+  const CtrlVals raw = load_ctrl(c.ctrl);
+  __builtin_amdgcn_sched_barrier(0);  // all of it under way before the first wait
+  const CtrlVals cv = with_eps(raw, eps, own != 0);
+  const SweepOut<D> o = sweep_out<D>(P, own_tile, kap2_of<ROW>(cv, kofs), (double)ins.tskip);
   double M;
   int J;
   warm_start<D>(in, o, j_hint, M, J);
@@ -738,7 +744,7 @@ __device__ __forceinline__ void sweep_block(const SideDev& out, const SideDev& i
   const double Rref = M > -INFINITY ? M : 0.0;
   if (!BARY && split == 0) part.ref[p] = Rref;
   const double gate = gate_min(M - o.tskip);  // a reduction over the wavefront: not under a lane's condition
-  const unsigned long long cand = __ballot(lane < nt && !(cub < gate));
+  const unsigned long long cand = __ballot(t < in.ntiles && !(cub < gate));
   const SplitSum r = sweep_split<D, MODE>(in, o, split, nsplit, M, J, cand);
   if (tile_count && lane == 0) tile_count[slot] = (unsigned)r.evaluated;
   if constexpr (BARY) {
@@ -752,30 +758,29 @@ __device__ __forceinline__ void sweep_block(const SideDev& out, const SideDev& i
   }
 }
 
-template <int D, int MODE>
+// The direction is a template parameter, as the dimension and the mode, so that
+// every argument sits at a fixed place and all of them are loaded at once.
+template <int D, int MODE, bool ROW>
 __global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSweepWaves))) void k_sweep(
-    LaunchCtx c, int transpose, int nsplit, double kap2_arg, int kofs) {
+    LaunchCtx c, int nsplit, double eps, int own, int kofs) {
   // blockIdx.x is the split and blockIdx.y the output block:
   // consecutive workgroups go to consecutive XCDs, so the splits of one output
   // block spread over all XCDs (a heavy output region does not load one XCD)
   // and each XCD reads the input tiles of only part of the splits (its L2
   // holds just those)
   const int slot = (blockIdx.y * gridDim.x + blockIdx.x) * (kSweepBlock / kTile) + threadIdx.x / kTile;
-  sweep_block<D, MODE>(transpose ? c.cols : c.rows, transpose ? c.rows : c.cols, nsplit, c.part, c.ctrl,
-                       kap2_arg, kofs, blockIdx.y, blockIdx.x, transpose == 0, c.tile_count, slot);
+  sweep_block<D, MODE, ROW>(c, nsplit, eps, own, kofs, blockIdx.y, blockIdx.x, c.tile_count, slot);
 }
 
 // Batched sweep: block i runs work item i = (problem, block of outputs, split)
 // of a list over several problems; the arithmetic per item is the same as in
 // the single-problem launch.
-template <int D, int MODE>
+template <int D, int MODE, bool ROW>
 __global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSweepWaves))) void k_sweep_batch(
-    const BatchItem* __restrict__ items, const LaunchCtx* __restrict__ descs, int transpose, int kofs) {
+    const BatchItem* __restrict__ items, const LaunchCtx* __restrict__ descs, int kofs) {
   const BatchItem it = items[blockIdx.x];
   const LaunchCtx& c = descs[it.prob];
-  sweep_block<D, MODE>(transpose ? c.cols : c.rows, transpose ? c.rows : c.cols,
-                       transpose ? c.splits_col : c.splits_row, c.part, c.ctrl, -1.0, kofs, it.blk, it.split,
-                       transpose == 0, nullptr, 0);
+  sweep_block<D, MODE, ROW>(c, ROW ? c.splits_row : c.splits_col, 0.0, 0, kofs, it.blk, it.split, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -796,8 +801,8 @@ struct SplitRec {
 __device__ __forceinline__ SplitRec split_rec(const PartialRec& q) { return SplitRec{q.dM, q.S, 0.0f, q.J}; }
 __device__ __forceinline__ SplitRec split_rec(const PartialCert& q) { return SplitRec{q.dM, q.S, q.N, q.J}; }
 
-template <bool CERT, typename Load>
-__device__ __forceinline__ Merged merge_splits_t(Load load, double R, int splits) {
+template <bool CERT, typename Load, typename Meanwhile>
+__device__ __forceinline__ Merged merge_splits_t(Load load, double R, int splits, Meanwhile meanwhile) {
   // The epilogue runs few waves, so its time is the number of memory round
   // trips: one pass over the split records, G of them requested together.
   // Past the last split the index is clamped to a valid record and its shift
@@ -814,10 +819,10 @@ __device__ __forceinline__ Merged merge_splits_t(Load load, double R, int splits
   auto batch = [&](int s0) {
     SplitRec q[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      q[g] = load(min(s0 + g, splits - 1));
-      q[g].dM += (s0 + g < splits) ? 0.0f : -INFINITY;
-    }
+    for (int g = 0; g < G; ++g) q[g] = load(min(s0 + g, splits - 1));
+    if (s0 == 0) meanwhile();
+#pragma unroll
+    for (int g = 0; g < G; ++g) q[g].dM += (s0 + g < splits) ? 0.0f : -INFINITY;
     float bm = -INFINITY;
     int bj = -1;
 #pragma unroll
@@ -855,14 +860,16 @@ __device__ __forceinline__ Merged merge_splits_t(Load load, double R, int splits
   return r;
 }
 
-__device__ __forceinline__ Merged merge_splits(const Partials& pt, bool cert, int splits, int np, int p) {
+template <bool CERT, typename Meanwhile>
+__device__ __forceinline__ Merged merge_splits(const Partials& pt, int splits, int np, int p, Meanwhile meanwhile) {
   const double R = pt.ref[p];
-  if (cert) {
+  if constexpr (CERT) {
     const PartialCert* rec = reinterpret_cast<const PartialCert*>(pt.rec) + p;
-    return merge_splits_t<true>([=](int s) { return split_rec(rec[(size_t)s * np]); }, R, splits);
+    return merge_splits_t<true>([=](int s) { return split_rec(rec[(size_t)s * np]); }, R, splits, meanwhile);
+  } else {
+    const PartialRec* rec = reinterpret_cast<const PartialRec*>(pt.rec) + p;
+    return merge_splits_t<false>([=](int s) { return split_rec(rec[(size_t)s * np]); }, R, splits, meanwhile);
   }
-  const PartialRec* rec = reinterpret_cast<const PartialRec*>(pt.rec) + p;
-  return merge_splits_t<false>([=](int s) { return split_rec(rec[(size_t)s * np]); }, R, splits);
 }
 
 // Packs the weights w of one tile for the sweeps: a least-squares plane
@@ -900,7 +907,8 @@ struct Geom {
 };
 template <int D>
 __device__ __forceinline__ Geom<D> load_geom(const SideDev& sd, int p) {
-  const TileGeom* t = sd.geom + __builtin_amdgcn_readfirstlane(min(p / kTile, sd.ntiles - 1));
+  typedef __attribute__((address_space(4))) const TileGeom cgeom;  // scalar loads
+  cgeom* t = (cgeom*)sd.geom + __builtin_amdgcn_readfirstlane(min(p / kTile, sd.ntiles - 1));
   Geom<D> g;
 #pragma unroll
   for (int d = 0; d < D; ++d) g.mb[d] = t->mb[d];
@@ -1064,56 +1072,63 @@ struct FinishPre {
 // of memory round trips: these loads are issued before the split records are
 // waited for.  Unconditional (p < np, and every array read here holds np
 // entries of the output side): a load under a branch is waited for there.
-template <int D>
-__device__ __forceinline__ FinishPre<D> finish_loads(const LaunchCtx& c, int transpose, int p, int kofs) {
-  const SideDev& out = transpose ? c.cols : c.rows;
+// ITER: an iteration's epilogue (the others read the control block alone).
+template <int D, bool ROW, bool ITER>
+__device__ __forceinline__ FinishPre<D> finish_loads(const LaunchCtx& c, int p) {
+  const SideDev& out = ROW ? c.rows : c.cols;
   FinishPre<D> f;
-  f.cv = load_ctrl(c.ctrl, kofs);
+  if (!ITER) {
+    f.cv = load_ctrl(c.ctrl);
+    return f;
+  }
   f.bo = load_offsets<D>(out, p);
-  const double* s_arr = transpose ? c.st.lb1 : c.st.la;
-  const double* t0_arr = transpose ? c.st.lt[0] : c.st.la;
-  const double* t1_arr = transpose ? c.st.lt[1] : c.st.la;
   f.lm = out.logmarg[p];
-  f.s = s_arr[p];
-  f.t0 = t0_arr[p];
-  f.t1 = t1_arr[p];
+  f.s = (ROW ? c.st.la : c.st.lb1)[p];
+  f.t0 = f.t1 = 0.0;
+  if (!ROW) {
+    f.t0 = c.st.lt[0][p];
+    f.t1 = c.st.lt[1][p];
+  }
   f.geom = load_geom<D>(out, p);
+  f.cv = load_ctrl(c.ctrl);
   return f;
+}
+
+constexpr bool finish_iterates(int kind) {
+  return kind == kFinishRow || kind == kFinishCol || kind == kFinishColCert;
 }
 
 // Epilogue of output p from its merged sums (whole wavefronts, one output
 // tile each).
-template <int D>
-__device__ __forceinline__ void finish_out(const LaunchCtx& c, int transpose, int kind,
-                                           double* __restrict__ lse_out, int p, const Merged& mg,
-                                           const FinishPre<D>& pre) {
-  const SideDev& out = transpose ? c.cols : c.rows;
+template <int D, int kind, bool ROW>
+__device__ __forceinline__ void finish_out(const LaunchCtx& c, double* __restrict__ lse_out, int p, int kofs,
+                                           const Merged& mg, const FinishPre<D>& pre) {
+  const SideDev& out = ROW ? c.rows : c.cols;
   const bool real = p < out.count;
-  const bool cert = (kind == kFinishColCert || kind == kFinishCertOnly);
-  const bool iter_kind = kind == kFinishRow || kind == kFinishCol || kind == kFinishColCert;
+  constexpr bool cert = kind == kFinishColCert;
   const double pre_lm = pre.lm, pre_s = pre.s, pre_t0 = pre.t0, pre_t1 = pre.t1;
   // the warm start of the next sweep of this side: only the iteration's own sweeps set it
-  if (real && iter_kind && mg.J >= 0) out.hint[p] = mg.J;
+  if (finish_iterates(kind) && real && mg.J >= 0) out.hint[p] = mg.J;
   const CtrlVals* ctrl = &pre.cv;
-  const long long k = ctrl->k;  // this iteration: the block's first plus the offset
+  const long long k = ctrl->k + kofs;  // this iteration: the block's first plus the offset
   const double lam = ctrl->lam;
 
-  if (kind == kFinishLse) {
+  if constexpr (kind == kFinishLse) {
     if (real) lse_out[out.perm[p]] = mg.lse;
     return;
   }
-  if (kind == kFinishPlanCol) {
+  if constexpr (kind == kFinishPlanCol) {
     // (X^T 1)_j = beta_j sum_i K_ij alpha_i
     if (real) c.plan_col[p] = exp(c.st.lb1[p] + mg.lse);
     return;
   }
   // two-sided rounding of the state plan (Altschuler, Weed and Rigollet 2017, Algorithm 2)
-  if (kind == kFinishRound1) {
+  if constexpr (kind == kFinishRound1) {
     // log x_i = min(0, log r_i - log (X 1)_i)
     if (real) c.plan_row[p] = fmin(0.0, out.logmarg[p] - (c.st.la[p] + mg.lse));
     return;
   }
-  if (kind == kFinishRound2) {
+  if constexpr (kind == kFinishRound2) {
     // X' = diag(x) X: log y_j = min(0, log c_j - log (X'^T 1)_j); deficit c_j - y_j (X'^T 1)_j
     if (real) {
       const double lcol = c.st.lb1[p] + mg.lse;
@@ -1125,7 +1140,7 @@ __device__ __forceinline__ void finish_out(const LaunchCtx& c, int transpose, in
     }
     return;
   }
-  if (kind == kFinishRound3) {
+  if constexpr (kind == kFinishRound3) {
     // X'' = diag(x) X diag(y): row deficit r_i - (X'' 1)_i and sum_j X''_ij C_ij
     if (real) {
       const double row2 = exp(c.st.la[p] + c.plan_row[p] + mg.lse);
@@ -1134,7 +1149,7 @@ __device__ __forceinline__ void finish_out(const LaunchCtx& c, int transpose, in
     }
     return;
   }
-  if (kind == kFinishCertOnly) {
+  if constexpr (kind == kFinishCertOnly) {
     // Algorithm 2 for the last finished iteration k-1 (k has been advanced)
     if (real) {
       c.st.mu[p] = ctrl->scale * mg.N / mg.S;
@@ -1142,15 +1157,15 @@ __device__ __forceinline__ void finish_out(const LaunchCtx& c, int transpose, in
     }
     return;
   }
-  if (kind == kFinishRepair) {
+  if constexpr (kind == kFinishRepair) {
     // p_i = A_i sum_j K_ij t_j (1 - e_j) = exp(log alpha-hat_i + LSE_i)
     c.st.pvec[p] = real ? exp(c.st.lah[p] + mg.lse) : 0.0;
     return;
   }
-  if (kind == kFinishRow) {
+  if constexpr (kind == kFinishRow) {
     // row update of Algorithm 1: the unrelaxed row scaling normalises the rows to r; the
     // relaxed one mixes it with the previous relaxed scaling, weight lambda on the new one
-    const double kap2 = kap2_col(*ctrl);
+    const double kap2 = kap2_of<false>(*ctrl, kofs);
     double colw = 0.0;
     if (real) {
       const double lah = pre_lm - mg.lse;
@@ -1172,38 +1187,42 @@ __device__ __forceinline__ void finish_out(const LaunchCtx& c, int transpose, in
     pack_weight_d<D>(c.rows, pre.geom, p, colw, kap2, pre.bo);
     return;
   }
-  // column epilogue (plain or certificate)
-  const int cur = (int)(k & 1), nxt = (int)((k + 1) & 1);
-  double lt_next = 0.0;
-  if (real) {
-    const double lbh = pre_lm - mg.lse;                 // log beta-hat^k = log c - LSE
-    const double lb1 = pre_s;
-    const double lb = fma(lam, lbh, (1.0 - lam) * lb1);  // log beta^k (rounding as for alpha)
-    if (cert) {
-      // certificate statistics of the intermediate plan's column (Prop. 3, Algorithm 2):
-      // its mean cost (cost-weighted over plain merged sums) and the log of its mass
-      c.st.mu[p] = ctrl->scale * mg.N / mg.S;
-      c.st.logs[p] = (cur ? pre_t1 : pre_t0) + mg.lse;
+  if constexpr (kind == kFinishCol || kind == kFinishColCert) {
+    // column epilogue (plain or certificate)
+    const int cur = (int)(k & 1), nxt = (int)((k + 1) & 1);
+    double lt_next = 0.0;
+    if (real) {
+      const double lbh = pre_lm - mg.lse;                 // log beta-hat^k = log c - LSE
+      const double lb1 = pre_s;
+      const double lb = fma(lam, lbh, (1.0 - lam) * lb1);  // log beta^k (rounding as for alpha)
+      if (cert) {
+        // certificate statistics of the intermediate plan's column (Prop. 3, Algorithm 2):
+        // its mean cost (cost-weighted over plain merged sums) and the log of its mass
+        c.st.mu[p] = ctrl->scale * mg.N / mg.S;
+        c.st.logs[p] = (cur ? pre_t1 : pre_t0) + mg.lse;
+      }
+      c.st.lbh[p] = lbh;
+      c.st.lb2[p] = lb1;
+      c.st.lb1[p] = lb;
+      // momentum for iteration k+1: log beta-tilde^k = log beta^k + (log beta^k - log beta^{k-1}) / lambda
+      lt_next = (ctrl->variant & kVarNoMomentum) ? lb : lb + (lam == 1.0 ? lb - lb1 : (lb - lb1) / lam);
+      c.st.lt[nxt][p] = lt_next;
     }
-    c.st.lbh[p] = lbh;
-    c.st.lb2[p] = lb1;
-    c.st.lb1[p] = lb;
-    // momentum for iteration k+1: log beta-tilde^k = log beta^k + (log beta^k - log beta^{k-1}) / lambda
-    lt_next = (ctrl->variant & kVarNoMomentum) ? lb : lb + (lb - lb1) / lam;
-    c.st.lt[nxt][p] = lt_next;
+    pack_weight_d<D>(c.cols, pre.geom, p, lt_next, kap2_of<true>(*ctrl, kofs + 1), pre.bo);
   }
-  pack_weight_d<D>(c.cols, pre.geom, p, lt_next, kap2_row(*ctrl, 1), pre.bo);
 }
 
 // Merge of the records in memory + epilogue of one tile (bx) of 64 outputs.
-template <int D>
-__device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, int kind, int splits,
-                                             double* __restrict__ lse_out, int bx, int kofs) {
-  const SideDev& out = transpose ? c.cols : c.rows;
+// The kind is a template parameter: compiled together, the kinds of all
+// dimensions were 13000 instructions, and the arguments of an iteration's
+// epilogue were loaded in a chain of scalar round trips behind its branches.
+template <int D, int kind, bool ROW>
+__device__ __forceinline__ void finish_block(const LaunchCtx& c, int splits, double* __restrict__ lse_out, int bx,
+                                             int kofs) {
+  const SideDev& out = ROW ? c.rows : c.cols;
   const int p = bx * kTile + threadIdx.x;
   const int np = out.np;
-  if (p >= np) return;
-  if (kind == kFinishPlanRow) {
+  if constexpr (kind == kFinishPlanRow) {
     // state plan: (X 1)_i = alpha_i sum_j K_ij beta_j, barycentre sum_j X_ij y_j / (X 1)_i
     const MergedBary mb = merge_bary(c.part.rec, splits, np, p);
     if (p < out.count) {
@@ -1214,20 +1233,30 @@ __device__ __forceinline__ void finish_block(const LaunchCtx& c, int transpose, 
         for (int d = 0; d < D; ++d) lse_out[(size_t)i * D + d] = c.origin[d] + mb.V[d];
       }
     }
-    return;
+  } else {
+    // the arguments of the later part loaded with the first ones, and the scalar
+    // loads of the control block and the tile geometry waited for while the
+    // records are under way (the compiler would issue each where it is used)
+    asm volatile("" ::"s"(c.ctrl), "s"(out.geom), "s"(out.A), "s"(out.tile), "s"(out.hint), "s"(c.part.rec));
+    const FinishPre<D> pre = finish_loads<D, ROW, finish_iterates(kind)>(c, p);
+    // the sweeps that gathered cost-weighted sums wrote certificate records
+    constexpr bool cert_rec = kind == kFinishColCert || kind == kFinishCertOnly || kind == kFinishRound3;
+    const Merged mg = merge_splits<cert_rec>(c.part, splits, np, p, [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::"s"(pre.cv.k), "s"(pre.cv.lam), "s"(pre.cv.scale), "s"(pre.cv.variant));
+      if constexpr (finish_iterates(kind)) {
+        asm volatile("" ::"s"(pre.cv.eta), "s"(pre.geom.cnt), "s"(pre.geom.cinv[0]), "s"(pre.geom.cinv[D]));
+#pragma unroll
+        for (int d = 0; d < D; ++d) asm volatile("" ::"s"(pre.geom.mb[d]));
+      }
+    });
+    finish_out<D, kind, ROW>(c, lse_out, p, kofs, mg, pre);
   }
-  const FinishPre<D> pre = finish_loads<D>(c, transpose, p, kofs);
-  // the sweeps that gathered cost-weighted sums wrote certificate records
-  const bool cert_rec = kind == kFinishColCert || kind == kFinishCertOnly || kind == kFinishRound3;
-  const Merged mg = merge_splits(c.part, cert_rec, splits, np, p);
-  finish_out<D>(c, transpose, kind, lse_out, p, mg, pre);
 }
 
-__global__ __launch_bounds__(kTile) void k_finish(LaunchCtx c, int transpose, int kind, int splits,
-                                                  double* __restrict__ lse_out, int kofs) {
-  if (c.dim == 1) finish_block<1>(c, transpose, kind, splits, lse_out, blockIdx.x, kofs);
-  else if (c.dim == 2) finish_block<2>(c, transpose, kind, splits, lse_out, blockIdx.x, kofs);
-  else finish_block<3>(c, transpose, kind, splits, lse_out, blockIdx.x, kofs);
+template <int D, int kind, bool ROW>
+__global__ __launch_bounds__(kTile) void k_finish(LaunchCtx c, int splits, double* __restrict__ lse_out, int kofs) {
+  finish_block<D, kind, ROW>(c, splits, lse_out, blockIdx.x, kofs);
 }
 
 // Advances the iteration counter by n after a block of n iterations (kernels of
@@ -1243,15 +1272,12 @@ __global__ void k_advance_batch(const LaunchCtx* __restrict__ descs, int count, 
 }
 
 // Batched merge + epilogue: block i runs item i = (problem, output tile).
+template <int D, int kind, bool ROW>
 __global__ __launch_bounds__(kTile) void k_finish_batch(const BatchItem* __restrict__ items,
-                                                        const LaunchCtx* __restrict__ descs, int transpose,
-                                                        int kind, int kofs) {
+                                                        const LaunchCtx* __restrict__ descs, int kofs) {
   const BatchItem it = items[blockIdx.x];
   const LaunchCtx& c = descs[it.prob];
-  const int splits = transpose ? c.splits_col : c.splits_row;
-  if (c.dim == 1) finish_block<1>(c, transpose, kind, splits, nullptr, it.blk, kofs);
-  else if (c.dim == 2) finish_block<2>(c, transpose, kind, splits, nullptr, it.blk, kofs);
-  else finish_block<3>(c, transpose, kind, splits, nullptr, it.blk, kofs);
+  finish_block<D, kind, ROW>(c, ROW ? c.splits_row : c.splits_col, nullptr, it.blk, kofs);
 }
 
 // lt and A_C of iteration k from the stored log beta^{k-1}, log beta^{k-2}.
@@ -1267,7 +1293,7 @@ __global__ __launch_bounds__(kBlock) void k_prologue(LaunchCtx c) {
     lt = (c.ctrl->variant & kVarNoMomentum) ? lb1 : lb1 + (lb1 - lb2) / lam;
     c.st.lt[k & 1][p] = lt;
   }
-  const double kap2 = kap2_row(load_ctrl(c.ctrl, 0));
+  const double kap2 = kap2_of<true>(load_ctrl(c.ctrl), 0);
   pack_weight(c.cols, c.dim, p, lt, kap2);
 }
 
@@ -1369,7 +1395,7 @@ __global__ __launch_bounds__(kBlock) void k_repair_pack(LaunchCtx c) {
     const double cj = c.cols.marg[p];
     if (s > cj) w = c.st.lt[k & 1][p] + log1p(-cj / s);
   }
-  const double kap2 = kap2_row(load_ctrl(c.ctrl, -1));
+  const double kap2 = kap2_of<true>(load_ctrl(c.ctrl), -1);
   pack_weight(c.cols, c.dim, p, w, kap2);
 }
 
@@ -1736,31 +1762,39 @@ __global__ __launch_bounds__(kBlock) void k_plan_entries(LaunchCtx c, const doub
 
 }  // namespace
 
-hipError_t launch_sweep_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, int dim,
-                              bool transpose, bool cert, int kofs, hipStream_t s) {
-  if (nitems <= 0) return hipSuccess;
-#define BDRS_SWEEPB(DD, CC)                                                                       \
-  hipLaunchKernelGGL((k_sweep_batch<DD, CC>), dim3(nitems), dim3(kSweepBlock), 0, s, items, descs,   \
-                     transpose ? 1 : 0, kofs)
-  switch (dim * 2 + (cert ? 1 : 0)) {
-    case 2: BDRS_SWEEPB(1, kSweepPlain); break;
-    case 3: BDRS_SWEEPB(1, kSweepCert); break;
-    case 4: BDRS_SWEEPB(2, kSweepPlain); break;
-    case 5: BDRS_SWEEPB(2, kSweepCert); break;
-    case 6: BDRS_SWEEPB(3, kSweepPlain); break;
-    case 7: BDRS_SWEEPB(3, kSweepCert); break;
+// Runs f with the dimension (1, 2, 3) as a constant.
+template <typename F>
+hipError_t by_dim(int dim, F f) {
+  switch (dim) {
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
     default: return hipErrorInvalidValue;
   }
-#undef BDRS_SWEEPB
   return hipGetLastError();
 }
 
-hipError_t launch_finish_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, bool transpose,
-                               FinishKind kind, int kofs, hipStream_t s) {
+hipError_t launch_sweep_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, int dim,
+                              bool transpose, bool cert, int kofs, hipStream_t s) {
   if (nitems <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finish_batch, dim3(nitems), dim3(kTile), 0, s, items, descs, transpose ? 1 : 0,
-                     (int)kind, kofs);
-  return hipGetLastError();
+  return by_dim(dim, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    auto* k = transpose ? (cert ? k_sweep_batch<D, kSweepCert, false> : k_sweep_batch<D, kSweepPlain, false>)
+                        : (cert ? k_sweep_batch<D, kSweepCert, true> : k_sweep_batch<D, kSweepPlain, true>);
+    hipLaunchKernelGGL(k, dim3(nitems), dim3(kSweepBlock), 0, s, items, descs, kofs);
+  });
+}
+
+hipError_t launch_finish_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, int dim, FinishKind kind,
+                               int kofs, hipStream_t s) {
+  if (nitems <= 0) return hipSuccess;
+  return by_dim(dim, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    auto* k = kind == kFinishRow   ? k_finish_batch<D, kFinishRow, true>
+              : kind == kFinishCol ? k_finish_batch<D, kFinishCol, false>
+                                   : k_finish_batch<D, kFinishColCert, false>;
+    hipLaunchKernelGGL(k, dim3(nitems), dim3(kTile), 0, s, items, descs, kofs);
+  });
 }
 
 hipError_t launch_advance(Ctrl* ctrl, int n, hipStream_t s) {
@@ -1797,57 +1831,55 @@ int choose_splits(int np_out, int ntiles_in) {
   return (ntiles_in + tps - 1) / tps;  // splits that own at least one tile
 }
 
-static double kap2_arg_of(const LaunchCtx& c, double eps_arg) {
-  return eps_arg > 0.0 ? kLog2eD * c.scale / eps_arg : -1.0;
+static hipError_t launch_sweep_mode(const LaunchCtx& c, bool transpose, SweepMode mode, int splits, double eps_arg,
+                                    int kofs) {
+  const SideDev& out = transpose ? c.cols : c.rows;
+  const dim3 grid(splits, out.np / kSweepBlock), block(kSweepBlock);  // x: split, y: output block (see k_sweep)
+  const int own = eps_arg > 0.0 ? 1 : 0;
+  return by_dim(c.dim, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    auto* k = mode == kSweepBary ? k_sweep<D, kSweepBary, true>
+              : transpose ? (mode == kSweepCert ? k_sweep<D, kSweepCert, false> : k_sweep<D, kSweepPlain, false>)
+                          : (mode == kSweepCert ? k_sweep<D, kSweepCert, true> : k_sweep<D, kSweepPlain, true>);
+    if (c.ev_start && c.ev_stop)
+      hipExtLaunchKernelGGL(k, grid, block, 0, c.stream, c.ev_start, c.ev_stop, 0u, c, splits, eps_arg, own, kofs);
+    else
+      hipLaunchKernelGGL(k, grid, block, 0, c.stream, c, splits, eps_arg, own, kofs);
+  });
 }
 
 hipError_t launch_sweep(const LaunchCtx& c, bool transpose, bool cert, int splits, double eps_arg, int kofs) {
-  const SideDev& out = transpose ? c.cols : c.rows;
-  dim3 grid(splits, out.np / kSweepBlock);  // x: split, y: output block (see k_sweep)
-  const double kap2 = kap2_arg_of(c, eps_arg);
-#define BDRS_SWEEP(DD, CC)                                                                                \
-  if (c.ev_start && c.ev_stop)                                                                            \
-    hipExtLaunchKernelGGL((k_sweep<DD, CC>), grid, dim3(kSweepBlock), 0, c.stream, c.ev_start, c.ev_stop, \
-                          0u, c, (int)(transpose ? 1 : 0), splits, kap2, kofs);                           \
-  else                                                                                                    \
-    hipLaunchKernelGGL((k_sweep<DD, CC>), grid, dim3(kSweepBlock), 0, c.stream, c, transpose ? 1 : 0, splits, \
-                       kap2, kofs)
-  switch (c.dim * 2 + (cert ? 1 : 0)) {
-    case 2: BDRS_SWEEP(1, kSweepPlain); break;
-    case 3: BDRS_SWEEP(1, kSweepCert); break;
-    case 4: BDRS_SWEEP(2, kSweepPlain); break;
-    case 5: BDRS_SWEEP(2, kSweepCert); break;
-    case 6: BDRS_SWEEP(3, kSweepPlain); break;
-    case 7: BDRS_SWEEP(3, kSweepCert); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef BDRS_SWEEP
-  return hipGetLastError();
+  return launch_sweep_mode(c, transpose, cert ? kSweepCert : kSweepPlain, splits, eps_arg, kofs);
 }
 
 hipError_t launch_sweep_bary(const LaunchCtx& c, int splits, double eps) {
-  const SideDev& out = c.rows;
-  dim3 grid(splits, out.np / kSweepBlock);  // x: split, y: output block (see k_sweep)
-#define BDRS_SWEEP(DD) \
-  hipLaunchKernelGGL((k_sweep<DD, kSweepBary>), grid, dim3(kSweepBlock), 0, c.stream, c, 0, splits, \
-                     kap2_arg_of(c, eps), 0)
-  switch (c.dim) {
-    case 1: BDRS_SWEEP(1); break;
-    case 2: BDRS_SWEEP(2); break;
-    case 3: BDRS_SWEEP(3); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef BDRS_SWEEP
-  return hipGetLastError();
+  return launch_sweep_mode(c, false, kSweepBary, splits, eps, 0);
 }
 
 hipError_t launch_finish(const LaunchCtx& c, bool transpose, FinishKind kind, int splits, double* lse_out,
                          int kofs) {
   // one wavefront per block (one tile of outputs), so the O(n) epilogue spreads over all CUs
-  const SideDev& out = transpose ? c.cols : c.rows;
-  hipLaunchKernelGGL(k_finish, dim3(out.ntiles), dim3(kTile), 0, c.stream, c, transpose ? 1 : 0,
-                     (int)kind, splits, lse_out, kofs);
-  return hipGetLastError();
+  const dim3 grid((transpose ? c.cols : c.rows).ntiles), block(kTile);
+  // (the kinds that do not pack weights are the same for every dimension)
+  const bool any_dim = !finish_iterates(kind) && kind != kFinishPlanRow;
+  return by_dim(any_dim ? 1 : c.dim, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    void (*k)(LaunchCtx, int, double*, int) = nullptr;
+    switch (kind) {
+      case kFinishRow: k = k_finish<D, kFinishRow, true>; break;
+      case kFinishCol: k = k_finish<D, kFinishCol, false>; break;
+      case kFinishColCert: k = k_finish<D, kFinishColCert, false>; break;
+      case kFinishPlanRow: k = k_finish<D, kFinishPlanRow, true>; break;
+      case kFinishLse: k = transpose ? k_finish<1, kFinishLse, false> : k_finish<1, kFinishLse, true>; break;
+      case kFinishRepair: k = k_finish<1, kFinishRepair, true>; break;
+      case kFinishCertOnly: k = k_finish<1, kFinishCertOnly, false>; break;
+      case kFinishPlanCol: k = k_finish<1, kFinishPlanCol, false>; break;
+      case kFinishRound1: k = k_finish<1, kFinishRound1, true>; break;
+      case kFinishRound2: k = k_finish<1, kFinishRound2, false>; break;
+      case kFinishRound3: k = k_finish<1, kFinishRound3, true>; break;
+    }
+    hipLaunchKernelGGL(k, grid, block, 0, c.stream, c, splits, lse_out, kofs);
+  });
 }
 
 hipError_t launch_prologue(const LaunchCtx& c) {

@@ -1700,45 +1700,53 @@ __global__ void k_export_factors(LaunchCtx c, int repaired, const double* __rest
 
 // Dense rows [row_begin, row_begin + nrows) of a factored plan, row-major in
 // original order: out[(i - row_begin) n + j] = exp(u_i + v_j - kap |x_i - y_j|^2)
-// (+ a_i b_j when R1), in float64 from the stored float32 coordinates.  One
-// thread per column holds y_j, v_j and b_j.  A block walks strips of
-// kEntryRows rows: its first wavefront loads the strip's slots, coordinates
-// and factors (one lane per row, two round trips per strip) into LDS, and
-// every thread then reads them from there for each row.  Write-bound: 8 bytes
-// per entry.
-constexpr int kEntryRows = 64;
+// (+ a_i b_j when R1), in float64 from the stored float32 coordinates.
+// Bound: writes, 8 bytes per entry (the float64 exponentials need less: a
+// shorter polynomial for them changed nothing), so every line is written whole:
+// a row's columns are split where its memory crosses 128 bytes, not at multiples
+// of kBlock, and a strip holds rows of one alignment (every period-th row;
+// lead is what the first block of such rows has before the row begins).
+// A thread holds y_j, v_j and b_j of its column; the first wavefront loads the
+// strip's slots, coordinates and factors (one lane per row) into LDS, and every
+// thread reads them from there for each row.  Consecutive blocks are neighbours
+// along a row, so that the blocks in flight fill whole rows; strips of 32 rows
+// leave many blocks to balance; the stores bypass the caches.
+// With the call, 4096 rows of 16384 entries (537 MB; a fill takes 81 us, launch
+// and wait about 20): 132 -> 110 us; of 16383 entries, which begin anywhere in a
+// line: 151 -> 113 us; 3001 rows of 2477: 33.4 -> 32.8 us.  Rows split at multiples
+// of kBlock instead: 182 us at 16383 entries (154 us through the caches); strips
+// of 64 / 48 / 24 rows at 16384: 12 us more / the same / the same; two columns
+// per thread: 3 us more.
+constexpr int kEntryRows = 32;
+constexpr int kLineDoubles = 16;  // 128 bytes
 template <int D, bool R1>
 __global__ __launch_bounds__(kBlock) void k_plan_entries(LaunchCtx c, const double* __restrict__ u,
                                                          const double* __restrict__ v,
                                                          const double* __restrict__ a,
                                                          const double* __restrict__ b, double kap,
-                                                         long long row_begin, long long nrows,
+                                                         long long row_begin, long long nrows, int skew,
+                                                         int period, long long strips,
                                                          double* __restrict__ out) {
   __shared__ float sx[D][kEntryRows];
   __shared__ double su[kEntryRows], sa[kEntryRows];
   const int n = c.cols.count;
-  const int j = blockIdx.y * kBlock + threadIdx.x;
-  const bool col = j < n;  // no early return: every thread reaches the barriers
-  double y[D];
-  double vj = 0.0, bj = 0.0;
-  if (col) {
+  for (long long sb = blockIdx.y; sb < strips; sb += gridDim.y) {
+    const int phase = (int)(sb & (period - 1));
+    const long long r0 = (sb - phase) * kEntryRows + phase;  // rows r0, r0 + period, ...
+    if (r0 >= nrows) continue;                               // the whole block
+    const int rows = (int)min((long long)kEntryRows, (nrows - r0 + period - 1) / period);
+    const int lead = (int)((skew + r0 * n) & (kLineDoubles - 1));
+    const long long jj = (long long)blockIdx.x * kBlock + threadIdx.x - lead;
+    const bool col = jj >= 0 && jj < n;  // no early return: every thread reaches the barriers
+    const int j = col ? (int)jj : 0;
     const int qj = c.cols.iperm[j];
+    double y[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) y[d] = (double)c.cols.abs[(size_t)d * c.cols.np + qj];
-    vj = v[j];
-    bj = R1 ? b[j] : 0.0;
-  } else {
-#pragma unroll
-    for (int d = 0; d < D; ++d) y[d] = 0.0;
-  }
-  const long long blocks = (nrows + kEntryRows - 1) / kEntryRows;
-  const long long last = row_begin + nrows - 1;
-  for (long long rb = blockIdx.x; rb < blocks; rb += gridDim.x) {
-    const long long r0 = rb * kEntryRows;
-    const int rows = (int)min((long long)kEntryRows, nrows - r0);
+    const double vj = v[j], bj = R1 ? b[j] : 0.0;
     __syncthreads();  // the previous strip's rows have been read
-    if (threadIdx.x < kEntryRows) {
-      const long long i = min(row_begin + r0 + threadIdx.x, last);
+    if ((int)threadIdx.x < rows) {
+      const long long i = row_begin + r0 + (long long)threadIdx.x * period;
       const int q = c.rows.iperm[i];
 #pragma unroll
       for (int d = 0; d < D; ++d) sx[d][threadIdx.x] = c.rows.abs[(size_t)d * c.rows.np + q];
@@ -1748,14 +1756,14 @@ __global__ __launch_bounds__(kBlock) void k_plan_entries(LaunchCtx c, const doub
     __syncthreads();
     if (!col) continue;
     double* o = out + (size_t)r0 * n + j;
-    for (int t = 0; t < rows; ++t) {
+    for (int t = 0; t < rows; ++t, o += (size_t)period * n) {
       double d2 = 0.0;
 #pragma unroll
       for (int d = 0; d < D; ++d) {
         const double e = (double)sx[d][t] - y[d];
         d2 = fma(e, e, d2);
       }
-      o[(size_t)t * n] = exp(su[t] + vj - kap * d2) + sa[t] * bj;
+      __builtin_nontemporal_store(exp(su[t] + vj - kap * d2) + sa[t] * bj, o);
     }
   }
 }
@@ -1954,22 +1962,21 @@ hipError_t launch_export_factors(const LaunchCtx& c, bool repaired, const double
 hipError_t launch_plan_entries(const LaunchCtx& c, const double* u, const double* v, const double* a,
                                const double* b, double kap, long long row_begin, long long nrows, double* out) {
   if (nrows <= 0 || c.cols.count <= 0) return hipSuccess;
-  const long long rblocks = (nrows + kEntryRows - 1) / kEntryRows;
-  const dim3 grid((unsigned)std::min(rblocks, 65536LL), (unsigned)((c.cols.count + kBlock - 1) / kBlock));
-#define BDRS_ENTRIES(DD, RR)                                                                        \
-  hipLaunchKernelGGL((k_plan_entries<DD, RR>), grid, dim3(kBlock), 0, c.stream, c, u, v, a, b, kap, \
-                     row_begin, nrows, out)
+  // rows period apart start at the same place in a line
+  int period = kLineDoubles;
+  while (period > 1 && (long long)c.cols.count * (period / 2) % kLineDoubles == 0) period /= 2;
+  const long long per_group = (long long)period * kEntryRows;
+  const long long strips = (nrows + per_group - 1) / per_group * period;
+  const int skew = (int)((uintptr_t)out / sizeof(double) % kLineDoubles);
+  const long long width = (long long)c.cols.count + (period > 1 || skew ? kLineDoubles - 1 : 0);
+  const dim3 grid((unsigned)((width + kBlock - 1) / kBlock), (unsigned)std::min(strips, 65535LL));
   const bool r1 = a != nullptr && b != nullptr;
-  switch (c.dim * 2 + (r1 ? 1 : 0)) {
-    case 2: BDRS_ENTRIES(1, false); break;
-    case 3: BDRS_ENTRIES(1, true); break;
-    case 4: BDRS_ENTRIES(2, false); break;
-    case 5: BDRS_ENTRIES(2, true); break;
-    case 6: BDRS_ENTRIES(3, false); break;
-    default: BDRS_ENTRIES(3, true); break;
-  }
-#undef BDRS_ENTRIES
-  return hipGetLastError();
+  return by_dim(c.dim, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    auto* k = r1 ? k_plan_entries<D, true> : k_plan_entries<D, false>;
+    hipLaunchKernelGGL(k, grid, dim3(kBlock), 0, c.stream, c, u, v, a, b, kap, row_begin, nrows, skew, period,
+                       strips, out);
+  });
 }
 
 hipError_t launch_scatter(const double* src, const int* perm, int count, double* dst, hipStream_t s) {

@@ -72,7 +72,7 @@ Layout make_layout(int m, int n, int dim, int reserve_row, int reserve_col, bool
   }
   L.splits_max = std::max(L.splits_row, L.splits_col);
   const int npmax = std::max(L.R.np, L.C.np);
-  L.cert_blocks = std::max(1, std::min(256, npmax / kBlock));
+  L.cert_blocks = std::max(1, std::min(kMaxCertBlocks, npmax / kBlock));
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;

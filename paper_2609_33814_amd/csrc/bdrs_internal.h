@@ -15,6 +15,7 @@ constexpr int kBlock = 256;       // threads per block of the O(n) kernels
 #endif
 constexpr int kSweepBlock = BDRS_SWEEP_BLOCK;
 constexpr int kPad = kSweepBlock > kBlock ? kSweepBlock : kBlock;  // np is a multiple of this
+constexpr int kMaxCertBlocks = 256;  // blocks of the certificate's and the statistics' partial sums
 constexpr int kCertSlots = 16;    // doubles in a certificate record
 
 // (output wavefront, split) pairs a sweep aims for: 4 per SIMD on 256 CUs

@@ -1373,12 +1373,18 @@ __global__ __launch_bounds__(kBlock) void k_plan_partial(LaunchCtx c) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_plan_final(LaunchCtx c, int nblocks) {
+  // all partials are requested at once and then combined in block order from
+  // LDS (one by one from memory it was a round trip per block: 45 us)
+  __shared__ double part[kMaxCertBlocks * 8];
+  for (int i = threadIdx.x; i < nblocks * 8; i += kBlock) part[i] = c.cert_part[i];
+  __syncthreads();
   if (threadIdx.x < 8) {
     const int i = threadIdx.x;
-    double a = c.cert_part[i];
+    const bool sum = i == 0 || i == 3 || i == 6;
+    double a = part[i];
     for (int b = 1; b < nblocks; ++b) {
-      const double x = c.cert_part[(size_t)b * 8 + i];
-      a = (i == 0 || i == 3 || i == 6) ? a + x : fmax(a, x);
+      const double x = part[b * 8 + i];
+      a = sum ? a + x : fmax(a, x);
     }
     c.plan_stats[i] = a;
   }

@@ -1206,9 +1206,14 @@ bdrs_status bdrs_get_state(bdrs_solver s, double* log_alpha, double* log_beta, d
   bdrs_status st = sync_k(s);
   if (st != BDRS_OK) return st;
   const LaunchCtx& c = s->ctx;
-  hipError_t e = hipSuccess;
+  StateVecs v{};
+  int nv = 0;
   auto sc = [&](const double* src, const SideDev& sd, double* dst) {
-    if (dst && e == hipSuccess) e = launch_scatter(src, sd.perm, sd.count, dst, c.stream);
+    if (!dst) return;
+    v.src[nv] = src;
+    v.dst[nv] = dst;
+    v.perm[nv] = sd.perm;
+    v.len[nv++] = sd.count;
   };
   sc(c.st.la, c.rows, log_alpha);
   sc(c.st.lb1, c.cols, log_beta);
@@ -1217,6 +1222,7 @@ bdrs_status bdrs_get_state(bdrs_solver s, double* log_alpha, double* log_beta, d
   sc(c.st.lbh, c.cols, log_beta_hat);
   // beta-tilde used by the last finished iteration k-1 sits in buffer (k-1) & 1
   sc(c.st.lt[(s->k + 1) & 1], c.cols, log_beta_tilde);
+  hipError_t e = launch_scatter(v, c.stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c.stream);
   if (e != hipSuccess) return hip_status(e, "get_state");
   if (iters_done) *iters_done = s->k;
@@ -1231,9 +1237,14 @@ bdrs_status bdrs_set_state(bdrs_solver s, const double* log_alpha, const double*
     return fail(BDRS_E_INVALID, "log_alpha, log_beta and log_beta_prev are required");
   if (iters_done < 0) return fail(BDRS_E_INVALID, "iters_done must be >= 0");
   const LaunchCtx& c = s->ctx;
-  hipError_t e = hipSuccess;
+  StateVecs v{};
+  int nv = 0;
   auto ga = [&](const double* src, const SideDev& sd, double* dst) {
-    if (src && e == hipSuccess) e = launch_gather(src, sd.perm, sd.np, dst, c.stream);
+    if (!src) return;
+    v.src[nv] = src;
+    v.dst[nv] = dst;
+    v.perm[nv] = sd.perm;
+    v.len[nv++] = sd.np;
   };
   ga(log_alpha, c.rows, c.st.la);
   ga(log_beta, c.cols, c.st.lb1);
@@ -1241,6 +1252,7 @@ bdrs_status bdrs_set_state(bdrs_solver s, const double* log_alpha, const double*
   ga(log_alpha_hat, c.rows, c.st.lah);
   ga(log_beta_hat, c.cols, c.st.lbh);
   ga(log_beta_tilde, c.cols, c.st.lt[(iters_done + 1) & 1]);
+  hipError_t e = launch_gather(v, c.stream);
   if (e != hipSuccess) return hip_status(e, "set_state");
   long long k = iters_done;
   HIPCHK(hipMemcpyAsync(&c.ctrl->k, &k, sizeof k, hipMemcpyHostToDevice, c.stream));
@@ -1294,10 +1306,9 @@ bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col
     return hip_status(e, "column sweep");
   if ((e = launch_plan_stats(c)) != hipSuccess) return hip_status(e, "statistics");
   // tile order -> caller order
-  if (row_marg && (e = launch_scatter(c.plan_row, c.rows.perm, c.rows.count, row_marg, c.stream)) != hipSuccess)
-    return hip_status(e, "row scatter");
-  if (col_marg && (e = launch_scatter(c.plan_col, c.cols.perm, c.cols.count, col_marg, c.stream)) != hipSuccess)
-    return hip_status(e, "column scatter");
+  const StateVecs v{{c.plan_row, c.plan_col}, {row_marg, col_marg}, {c.rows.perm, c.cols.perm},
+                    {c.rows.count, c.cols.count}};
+  if ((e = launch_scatter(v, c.stream)) != hipSuccess) return hip_status(e, "marginals");
   double h[kCertSlots];
   HIPCHK(hipMemcpyAsync(h, c.plan_stats, sizeof(double) * 8, hipMemcpyDeviceToHost, c.stream));
   HIPCHK(hipStreamSynchronize(c.stream));
@@ -1426,10 +1437,7 @@ bdrs_status bdrs_plan_entries(bdrs_solver s, const double* log_u, const double* 
 bdrs_status bdrs_get_hints(bdrs_solver s, int32_t* row_hint, int32_t* col_hint) {
   if (!s) return fail(BDRS_E_INVALID, "solver is NULL");
   const LaunchCtx& c = s->ctx;
-  hipError_t e = hipSuccess;
-  if (row_hint) e = launch_hints_out(c.rows.hint, c.rows.perm, c.cols.perm, c.rows.count, row_hint, c.stream);
-  if (e == hipSuccess && col_hint)
-    e = launch_hints_out(c.cols.hint, c.cols.perm, c.rows.perm, c.cols.count, col_hint, c.stream);
+  hipError_t e = launch_hints_out(c, row_hint, col_hint);
   if (e == hipSuccess) e = hipStreamSynchronize(c.stream);
   return e == hipSuccess ? BDRS_OK : hip_status(e, "get_hints");
 }
@@ -1437,10 +1445,7 @@ bdrs_status bdrs_get_hints(bdrs_solver s, int32_t* row_hint, int32_t* col_hint) 
 bdrs_status bdrs_set_hints(bdrs_solver s, const int32_t* row_hint, const int32_t* col_hint) {
   if (!s) return fail(BDRS_E_INVALID, "solver is NULL");
   const LaunchCtx& c = s->ctx;
-  hipError_t e = hipSuccess;
-  if (row_hint) e = launch_hints_in(row_hint, c.rows.perm, c.cols.iperm, c.cols.count, c.rows.np, c.rows.hint, c.stream);
-  if (e == hipSuccess && col_hint)
-    e = launch_hints_in(col_hint, c.cols.perm, c.rows.iperm, c.rows.count, c.cols.np, c.cols.hint, c.stream);
+  hipError_t e = launch_hints_in(c, row_hint, col_hint);
   if (e == hipSuccess) e = hipStreamSynchronize(c.stream);
   return e == hipSuccess ? BDRS_OK : hip_status(e, "set_hints");
 }

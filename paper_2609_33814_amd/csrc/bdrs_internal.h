@@ -221,13 +221,20 @@ hipError_t launch_export_factors(const LaunchCtx& c, bool repaired, const double
 // dense rows [row_begin, row_begin + nrows) of a factored plan (kap = cost scale / eps)
 hipError_t launch_plan_entries(const LaunchCtx& c, const double* u, const double* v, const double* a,
                                const double* b, double kap, long long row_begin, long long nrows, double* out);
-hipError_t launch_scatter(const double* src, const int* perm, int count, double* dst, hipStream_t s);
-hipError_t launch_gather(const double* src, const int* perm, int np, double* dst, hipStream_t s);
-// hints: to original order (out[perm_out[p]] = perm_in[hint[p]]) and back
-hipError_t launch_hints_out(const int* hint, const int* perm_out, const int* perm_in, int count, int* dst,
-                            hipStream_t s);
-hipError_t launch_hints_in(const int* src, const int* perm_out, const int* iperm_in, int count_in, int np,
-                           int* hint, hipStream_t s);
+// vectors between tile order and the caller's order (null ones are skipped);
+// gather: len is the padded length, scatter: the number of points
+constexpr int kStateVecs = 6;
+struct StateVecs {
+  const double* src[kStateVecs];
+  double* dst[kStateVecs];
+  const int* perm[kStateVecs];
+  int len[kStateVecs];
+};
+hipError_t launch_scatter(const StateVecs& v, hipStream_t s);
+hipError_t launch_gather(const StateVecs& v, hipStream_t s);
+// warm-start hints of both sides to the caller's order and back (null: skipped)
+hipError_t launch_hints_out(const LaunchCtx& c, int* row_hint, int* col_hint);
+hipError_t launch_hints_in(const LaunchCtx& c, const int* row_hint, const int* col_hint);
 
 // Batched phases over the problems in `descs` (device array of LaunchCtx).
 hipError_t launch_sweep_batch(const BatchItem* items, int nitems, const LaunchCtx* descs, int dim,

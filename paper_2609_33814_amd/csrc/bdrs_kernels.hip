@@ -1644,34 +1644,42 @@ __global__ __launch_bounds__(kBlock) void k_count_tiles(const unsigned* __restri
   }
 }
 
-__global__ void k_scatter(const double* __restrict__ src, const int* __restrict__ perm, int count,
-                          double* __restrict__ dst) {
+// Up to kStateVecs vectors between tile order and the caller's order in one
+// launch (a state is six of them, and a launch costs more than a vector):
+// out: dst[perm[p]] = src[p]; in: dst[p] = src[perm[p]] over the padded length.
+__global__ void k_scatter(StateVecs v) {
   const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p < count) dst[perm[p]] = src[p];
+#pragma unroll
+  for (int i = 0; i < kStateVecs; ++i)
+    if (v.dst[i] && p < v.len[i]) v.dst[i][v.perm[i][p]] = v.src[i][p];
 }
 
-__global__ void k_hints_out(const int* __restrict__ hint, const int* __restrict__ perm_out,
-                            const int* __restrict__ perm_in, int count, int* __restrict__ dst) {
+__global__ void k_gather(StateVecs v) {
   const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p < count) {
-    const int j = hint[p];
-    dst[perm_out[p]] = j >= 0 ? perm_in[j] : -1;
+#pragma unroll
+  for (int i = 0; i < kStateVecs; ++i)
+    if (v.src[i] && p < v.len[i]) v.dst[i][p] = v.src[i][v.perm[i][p]];
+}
+
+// Hints to the caller's order (dst[perm_out[p]] = perm_in[hint[p]]) and back,
+// both sides in one launch (a null pointer skips one).
+__global__ void k_hints_out(SideDev rows, SideDev cols, int* __restrict__ row_hint, int* __restrict__ col_hint) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (row_hint && p < rows.count) row_hint[rows.perm[p]] = rows.hint[p] >= 0 ? cols.perm[rows.hint[p]] : -1;
+  if (col_hint && p < cols.count) col_hint[cols.perm[p]] = cols.hint[p] >= 0 ? rows.perm[cols.hint[p]] : -1;
+}
+
+__global__ void k_hints_in(SideDev rows, SideDev cols, const int* __restrict__ row_hint,
+                           const int* __restrict__ col_hint) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (row_hint && p < rows.np) {
+    const int j = row_hint[rows.perm[p]];
+    rows.hint[p] = (j >= 0 && j < cols.count) ? cols.iperm[j] : -1;
   }
-}
-
-__global__ void k_hints_in(const int* __restrict__ src, const int* __restrict__ perm_out,
-                           const int* __restrict__ iperm_in, int count_in, int np, int* __restrict__ hint) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p < np) {
-    const int j = src[perm_out[p]];
-    hint[p] = (j >= 0 && j < count_in) ? iperm_in[j] : -1;
+  if (col_hint && p < cols.np) {
+    const int j = col_hint[cols.perm[p]];
+    cols.hint[p] = (j >= 0 && j < rows.count) ? rows.iperm[j] : -1;
   }
-}
-
-__global__ void k_gather(const double* __restrict__ src, const int* __restrict__ perm, int np,
-                         double* __restrict__ dst) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p < np) dst[p] = src[perm[p]];
 }
 
 // Factors of a feasible plan X_ij = exp(u_i + v_j - C_ij / eps) + a_i b_j, in
@@ -1985,31 +1993,40 @@ hipError_t launch_plan_entries(const LaunchCtx& c, const double* u, const double
   });
 }
 
-hipError_t launch_scatter(const double* src, const int* perm, int count, double* dst, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter, dim3((count + kBlock - 1) / kBlock), dim3(kBlock), 0, s, src, perm, count, dst);
+static int longest(const StateVecs& v) {
+  int n = 0;
+  for (int i = 0; i < kStateVecs; ++i)
+    if (v.src[i] && v.dst[i]) n = std::max(n, v.len[i]);
+  return n;
+}
+
+hipError_t launch_scatter(const StateVecs& v, hipStream_t s) {
+  const int n = longest(v);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_scatter, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, v);
   return hipGetLastError();
 }
 
-hipError_t launch_hints_out(const int* hint, const int* perm_out, const int* perm_in, int count, int* dst,
-                            hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hints_out, dim3((count + kBlock - 1) / kBlock), dim3(kBlock), 0, s, hint, perm_out, perm_in,
-                     count, dst);
+hipError_t launch_gather(const StateVecs& v, hipStream_t s) {
+  const int n = longest(v);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_gather, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, v);
   return hipGetLastError();
 }
 
-hipError_t launch_hints_in(const int* src, const int* perm_out, const int* iperm_in, int count_in, int np,
-                           int* hint, hipStream_t s) {
-  if (np <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hints_in, dim3((np + kBlock - 1) / kBlock), dim3(kBlock), 0, s, src, perm_out, iperm_in,
-                     count_in, np, hint);
+hipError_t launch_hints_out(const LaunchCtx& c, int* row_hint, int* col_hint) {
+  if (!row_hint && !col_hint) return hipSuccess;
+  const int n = std::max(c.rows.count, c.cols.count);
+  hipLaunchKernelGGL(k_hints_out, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, c.stream, c.rows, c.cols,
+                     row_hint, col_hint);
   return hipGetLastError();
 }
 
-hipError_t launch_gather(const double* src, const int* perm, int np, double* dst, hipStream_t s) {
-  if (np <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather, dim3((np + kBlock - 1) / kBlock), dim3(kBlock), 0, s, src, perm, np, dst);
+hipError_t launch_hints_in(const LaunchCtx& c, const int* row_hint, const int* col_hint) {
+  if (!row_hint && !col_hint) return hipSuccess;
+  const int n = std::max(c.rows.np, c.cols.np);
+  hipLaunchKernelGGL(k_hints_in, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, c.stream, c.rows, c.cols,
+                     row_hint, col_hint);
   return hipGetLastError();
 }
 

@@ -461,13 +461,9 @@ bdrs_status enqueue_iteration(bdrs_solver s, bool cert, int kofs) {
 // re-derives the packed sweep weights from the dual state (after bdrs_lse or a repair pass)
 bdrs_status repack(bdrs_solver s) {
   const LaunchCtx& c = s->ctx;
-  hipError_t e;
-  if ((e = launch_prologue(c)) != hipSuccess) return hip_status(e, "prologue");
-  if (s->k > 0) {
-    // rows.A <- log alpha-hat of iteration k-1 with that iteration's temperature
-    if ((e = launch_pack_rows_from_lah(c, eps_row_at(s, s->k - 1))) != hipSuccess) return hip_status(e, "repack");
-    s->packed_rows = true;
-  }
+  const hipError_t e = launch_repack(c);
+  if (e != hipSuccess) return hip_status(e, "repack");
+  if (s->k > 0) s->packed_rows = true;
   return BDRS_OK;
 }
 
@@ -1280,12 +1276,22 @@ bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps, const double*
   const bool tr = transpose != 0;
   const int splits = tr ? s->L.splits_col : s->L.splits_row;
   hipError_t e;
+  if (!s->read_ev) HIPCHK(hipEventCreateWithFlags(&s->read_ev, hipEventDisableTiming));
   if ((e = launch_pack(c, tr, w, eps)) != hipSuccess) return hip_status(e, "pack");
-  bdrs_status st = sync_k(s);
-  if (st != BDRS_OK) return st;
-  if ((e = sweep(s, tr, false, kFinishLse, splits, eps, out)) != hipSuccess) return hip_status(e, "sweep");
+  HIPCHK(hipEventRecord(s->read_ev, c.stream));
+  e = sweep(s, tr, false, kFinishLse, splits, eps, out);
   s->packed_rows = false;
-  return repack(s);
+  const bdrs_status st = e == hipSuccess ? repack(s) : BDRS_OK;
+  // on return w has been read and what was enqueued before has ended; the wait
+  // comes last, so that the launches do not wait for it (a wait with a copy of
+  // k before the sweep left the GPU idle for 10 us of 37)
+  const hipError_t ew = hipEventSynchronize(s->read_ev);
+  if (e != hipSuccess) return hip_status(e, "sweep");
+  if (ew != hipSuccess) {
+    s->packed_rows = false;  // nothing may have run (a stream under capture)
+    return hip_status(ew, "lse");
+  }
+  return st;
 }
 
 bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col_marg, bdrs_plan_stats* out) {
@@ -1513,6 +1519,7 @@ bdrs_status bdrs_destroy(bdrs_solver s) {
   hipError_t e = hipStreamSynchronize(s->ctx.stream);
   // teardown: nothing to report
   for (hipEvent_t ev : s->ev_pool) (void)hipEventDestroy(ev);
+  if (s->read_ev) (void)hipEventDestroy(s->read_ev);
   if (s->blk_exec) (void)hipGraphExecDestroy(s->blk_exec);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   delete s;

@@ -201,7 +201,7 @@ hipError_t launch_finish(const LaunchCtx& c, bool transpose, FinishKind kind, in
 hipError_t launch_advance(Ctrl* ctrl, int n, hipStream_t s);
 hipError_t launch_prologue(const LaunchCtx& c);                       // lt and A_C for iteration k
 hipError_t launch_pack(const LaunchCtx& c, bool transpose, const double* w, double eps);
-hipError_t launch_pack_rows_from_lah(const LaunchCtx& c, double eps);
+hipError_t launch_repack(const LaunchCtx& c);  // prologue, and rows.A from log alpha-hat of iteration k - 1
 // state plan: input side packed from the state (columns: log beta, rows: log alpha),
 // plus the rounding's log factors (plan_col / plan_row) when with_factors
 hipError_t launch_pack_state(const LaunchCtx& c, bool transpose, double eps, bool with_factors = false);

@@ -1281,8 +1281,8 @@ __global__ __launch_bounds__(kTile) void k_finish_batch(const BatchItem* __restr
 }
 
 // lt and A_C of iteration k from the stored log beta^{k-1}, log beta^{k-2}.
-__global__ __launch_bounds__(kBlock) void k_prologue(LaunchCtx c) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
+__device__ __forceinline__ void prologue_block(const LaunchCtx& c, int bx) {
+  const int p = bx * kBlock + threadIdx.x;
   if (p >= c.cols.np) return;
   const long long k = c.ctrl->k;
   const double lam = c.ctrl->lam;
@@ -1297,6 +1297,29 @@ __global__ __launch_bounds__(kBlock) void k_prologue(LaunchCtx c) {
   pack_weight(c.cols, c.dim, p, lt, kap2);
 }
 
+__global__ __launch_bounds__(kBlock) void k_prologue(LaunchCtx c) { prologue_block(c, blockIdx.x); }
+
+// Restores both sides' weights after the sweep buffers were used otherwise: the
+// first col_blocks blocks are the prologue's, the others write rows.A from log
+// alpha-hat of iteration k - 1 at that iteration's temperature (none at k = 0).
+// One launch for both, and the temperature from the control block, so that the
+// host need not read k back first.
+__global__ __launch_bounds__(kBlock) void k_repack(LaunchCtx c, int col_blocks) {
+  if ((int)blockIdx.x < col_blocks) return prologue_block(c, blockIdx.x);
+  const int p = (blockIdx.x - col_blocks) * kBlock + threadIdx.x;
+  const long long k = c.ctrl->k - 1;
+  if (p >= c.rows.np || k < 0) return;
+  double eps;
+  {
+#pragma clang fp contract(off)  // as the host rounds it
+    const double den = c.ctrl->lam * (double)k + 1.0;
+    eps = c.ctrl->variant & kVarOldKernel ? (k >= 1 ? c.ctrl->eta / (double)k : c.ctrl->eta * kFarTemperature)
+                                          : c.ctrl->eta / den;
+  }
+  const double kap2 = kLog2eD * c.ctrl->scale / eps;
+  pack_weight(c.rows, c.dim, p, p < c.rows.count ? c.st.lah[p] : 0.0, kap2);
+}
+
 // A of the input side from caller weights w (original order), for bdrs_lse.
 __global__ __launch_bounds__(kBlock) void k_pack(LaunchCtx c, int transpose, const double* __restrict__ w,
                                                  double eps) {
@@ -1306,14 +1329,6 @@ __global__ __launch_bounds__(kBlock) void k_pack(LaunchCtx c, int transpose, con
   const double kap2 = kLog2eD * c.ctrl->scale / eps;
   const double wv = p < in.count ? w[in.perm[p]] : 0.0;
   pack_weight(in, c.dim, p, wv, kap2);
-}
-
-// rows.A from the stored log alpha-hat (re-pack after the sweep buffers were reused).
-__global__ __launch_bounds__(kBlock) void k_pack_rows(LaunchCtx c, double eps) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= c.rows.np) return;
-  const double kap2 = kLog2eD * c.ctrl->scale / eps;
-  pack_weight(c.rows, c.dim, p, p < c.rows.count ? c.st.lah[p] : 0.0, kap2);
 }
 
 // State-plan weights of the input side: log beta^{k-1} on the columns (row sums
@@ -1915,8 +1930,9 @@ hipError_t launch_pack(const LaunchCtx& c, bool transpose, const double* w, doub
   return hipGetLastError();
 }
 
-hipError_t launch_pack_rows_from_lah(const LaunchCtx& c, double eps) {
-  hipLaunchKernelGGL(k_pack_rows, dim3(c.rows.np / kBlock), dim3(kBlock), 0, c.stream, c, eps);
+hipError_t launch_repack(const LaunchCtx& c) {
+  const int cols = c.cols.np / kBlock;
+  hipLaunchKernelGGL(k_repack, dim3(cols + c.rows.np / kBlock), dim3(kBlock), 0, c.stream, c, cols);
   return hipGetLastError();
 }
 

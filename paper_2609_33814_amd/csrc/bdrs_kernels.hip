@@ -13,8 +13,8 @@
 //     w2_q - kappa2 |a - b_q|^2 = base + B . b_q + A_q,
 //     base = alpha - kappa2 |a|^2,  B = gamma + 2 kappa2 a,
 //     A_q = w2_q - alpha - gamma . b_q - kappa2 |b_q|^2   (written by the producing epilogue),
-// i.e. d FMAs and one add per entry, then one v_exp_f32 and one add.  For d > 1
-// the plain sweep forms the exponents on the matrix cores (sweep_split_mfma).
+// i.e. d FMAs and one add per entry, then one v_exp_f32 and one add.  The plain
+// sweep forms the exponents on the matrix cores (sweep_split_mfma).
 //
 // Precision split.  The weights w grow like g / eps as the temperature falls,
 // so float32 values of that size would carry absolute errors u |g| / eps.  The
@@ -407,34 +407,36 @@ __device__ __forceinline__ float tile_max(gfloat* __restrict__ offs, gfloat* __r
 // picks the candidates; per candidate the lane bounds its own exponents, the
 // wavefront skips the tile when no lane can see it, else the whole 64 x 64
 // block of exponents z_qp = cm_p + B_p . b_q + A_q is a product of inner
-// dimension D + 2, taken in rank-one steps of v_mfma_f32_32x32x1 (two blocks
-// of 32 outputs, 32 inputs): each step is one IEEE fused multiply-add per
+// dimension D + 2, taken in rank-one steps of v_mfma_f32_16x16x1 (four blocks
+// of 16 outputs, 16 inputs): each step is one IEEE fused multiply-add per
 // element, so the chain cm, + B_0 b_0, ..., + 1 A_q rounds exactly as the
-// scalar code of the other modes does.  Input operands: lane l holds point
+// scalar code of the other modes does.  The chain's first step is the same for
+// all inputs, so it is taken once per tile and the four quarters of the tile's
+// points start from its registers.  Input operands: lane l holds point
 // pt(l) of the tile, one coalesced load per coordinate, and cbsz/abid
-// broadcast either half of them to both blocks.  Result element i of a block
-// is row 8 (i / 4) + 4 (lane / 32) + i % 4; with bits 1 and 2 of the point
-// index swapped (pt) the lower half wave holds the points q = 0, 1 mod 4 and
-// the upper half q = 2, 3 mod 4, in order, so each lane's two running sums per
-// output are the sums over q mod 4 in point order and one exchange between
-// the half waves (v_permlane32_swap) brings the four together.
+// broadcast one quarter of them to all blocks.  Result element i is block i / 4,
+// row 4 (lane / 16) + i % 4; with the two pairs of bits of the point's index in
+// its quarter exchanged (pt) the lanes of quarter g of the wavefront hold the
+// points q = g mod 4, in order, so each lane's running sum per output block is
+// the sum over q = g mod 4 in point order, and three exchanges between the
+// quarters bring the four together.
 //
 // Bound: the float32 VALU / matrix pipe, one for both on gfx950 (work of the
 // two kinds from different wavefronts takes the sum of their times).  Measured
 // cycles per wavefront instruction: fused multiply-add 4.2 (any form with three
 // register operands or a scalar one), exp2 8.2, add 2.5 (4 after an exp2),
-// rank-one step 2.03 per input.  So an entry takes 20.9 cycles here against
-// 25.8 on the VALU for d = 3, 18.8 against 21.6 for d = 2, 16.8 against 17.4
+// rank-one step 2.03 per input.  So an entry takes 19.4 cycles here against
+// 25.8 on the VALU for d = 3, 17.3 against 21.6 for d = 2, 15.3 against 17.4
 // for d = 1; and the tile data comes by one vector load per coordinate instead
-// of a chain of scalar ones.  Dense sweeps of 1 M points per side (d = 3):
-// 194 -> 173 ms; 50 iterations of two 251x251 grids (d = 2, 7% of the entries):
-// 9.46 -> 8.48 ms.  For d = 1 the two are even on paper and the VALU form,
-// which needs fewer registers, measured 3% faster (30000 x 20000 points, 50
-// iterations: 5.53 against 5.69 ms), so only d > 1 comes here.  The next
-// candidate's record and points are requested while the current one is tested
-// and evaluated.  Five wavefronts per SIMD (kSweepWaves) measured best: four
-// 2% slower, seven and eight spill or lose the overlap of the two halves.
-typedef float f32x32 __attribute__((ext_vector_type(32)));
+// of a chain of scalar ones.  With blocks of 32 x 32 (v_mfma_f32_32x32x1), whose
+// registers leave no room for the bases, the first step was taken for each
+// half: 1.5 cycles more per entry.
+// Dense sweeps of 1 M points per side (d = 3): 194 ms on the VALU, 173 with halves,
+// 164 with quarters; 50 iterations of two 251x251 grids (d = 2, 7% of the
+// entries): 9.46, 8.31, 8.03 ms; of 30000 x 20000 points on a line: 5.19 ms on the
+// VALU, 5.02 with quarters.  The next candidate's record and points are requested
+// while the current one is tested and evaluated.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 template <int D>
@@ -451,42 +453,46 @@ __device__ __forceinline__ TilePts<D> load_points(const SweepIn& in, int t, int 
   return v;
 }
 
-// Exponents of 32 inputs (half H of the tile's points) against 64 outputs.
+// Exponents of 16 inputs (quarter H of the tile's points) against 64 outputs,
+// from the outputs' bases.
 template <int D, int H>
-__device__ __forceinline__ f32x32 exponents(const TilePts<D>& q, const float (&B)[D], float cm) {
-  f32x32 z = {};
-  z = __builtin_amdgcn_mfma_f32_32x32x1f32(1.0f, cm, z, 1, H, 0);
+__device__ __forceinline__ f32x16 exponents(const TilePts<D>& q, const float (&B)[D], f32x16 z) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) z = __builtin_amdgcn_mfma_f32_32x32x1f32(q.b[d], B[d], z, 1, H, 0);
-  return __builtin_amdgcn_mfma_f32_32x32x1f32(q.a, 1.0f, z, 1, H, 0);
+  for (int d = 0; d < D; ++d) z = __builtin_amdgcn_mfma_f32_16x16x1f32(q.b[d], B[d], z, 2, H, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x1f32(q.a, 1.0f, z, 2, H, 0);
 }
 
 // sum_q 2^{z_q} over the tile's 64 points for the lane's own output.
 template <int D>
 __device__ __forceinline__ float tile_sum(const TilePts<D>& pts, const float (&B)[D], float cm) {
-  // block 0 (outputs 0-31): x0, x1; block 1 (outputs 32-63): y0, y1
-  f32x32 z = exponents<D, 0>(pts, B, cm);
-  float x0 = fast_exp2(z[0]), x1 = fast_exp2(z[1]), y0 = fast_exp2(z[16]), y1 = fast_exp2(z[17]);
+  f32x16 base = {};
+  base = __builtin_amdgcn_mfma_f32_16x16x1f32(1.0f, cm, base, 0, 0, 0);
+  // x[i]: outputs 16 i + lane % 16
+  float x[4];
+  f32x16 z = exponents<D, 0>(pts, B, base);
 #pragma unroll
-  for (int i = 2; i < 16; i += 2) {
-    x0 += fast_exp2(z[i]);
-    x1 += fast_exp2(z[i + 1]);
-    y0 += fast_exp2(z[16 + i]);
-    y1 += fast_exp2(z[17 + i]);
-  }
-  z = exponents<D, 1>(pts, B, cm);
+  for (int i = 0; i < 4; ++i) x[i] = fast_exp2(z[4 * i]);
 #pragma unroll
-  for (int i = 0; i < 16; i += 2) {
-    x0 += fast_exp2(z[i]);
-    x1 += fast_exp2(z[i + 1]);
-    y0 += fast_exp2(z[16 + i]);
-    y1 += fast_exp2(z[17 + i]);
-  }
-  // lower lanes hold q = 0, 1 mod 4 and upper lanes q = 2, 3 mod 4 of outputs
-  // lane % 32 (x) and 32 + lane % 32 (y): after the swap each lane has both
-  // pairs of its own output
-  const u32x2 w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0 + x1), __float_as_uint(y0 + y1), false, false);
-  return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+  for (int e = 1; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] += fast_exp2(z[4 * i + e]);
+  auto add = [&](const f32x16& y) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] += fast_exp2(y[4 * i + e]);
+  };
+  add(exponents<D, 1>(pts, B, base));
+  add(exponents<D, 2>(pts, B, base));
+  add(exponents<D, 3>(pts, B, base));
+  // quarter g of the wavefront holds q = g mod 4 of all four output blocks: swaps
+  // between neighbouring quarters, then between the halves, bring the four sums
+  // of a lane's own output together
+  auto swapped_sum = [](u32x2 w) { return __uint_as_float(w[0]) + __uint_as_float(w[1]); };
+  auto bits = [](float v) { return __float_as_uint(v); };
+  const float u = swapped_sum(__builtin_amdgcn_permlane16_swap(bits(x[0]), bits(x[1]), false, false));
+  const float v = swapped_sum(__builtin_amdgcn_permlane16_swap(bits(x[2]), bits(x[3]), false, false));
+  return swapped_sum(__builtin_amdgcn_permlane32_swap(bits(u), bits(v), false, false));
 }
 
 // Exponent of a tile for a lane: slope B = gamma + 2 kappa2 a (rounded once)
@@ -509,7 +515,7 @@ __device__ __forceinline__ SplitSum sweep_split_mfma(const SweepIn& in, const Sw
                                                       double M, int J, unsigned long long cand) {
   const int lane = (int)(threadIdx.x & (kTile - 1));
   const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
-  const int pt = (lane & ~6) | ((lane & 2) << 1) | ((lane & 4) >> 1);
+  const int pt = (lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3);
   SplitSum r{M, 0.0f, 0.0f, {0.0f, 0.0f, 0.0f}, J, 0};
   double Mth = M + kThresh;      // the exact-max gate, updated with M
   double Mlo = M - o.tskip;      // the skip gate, updated with M
@@ -560,7 +566,7 @@ __device__ __forceinline__ SplitSum sweep_split_mfma(const SweepIn& in, const Sw
 
 // The same walk with every entry evaluated on the VALU: the certificate sweep
 // (cost-weighted sum N) and the barycentric sweep (coordinate sums V), whose
-// weighted sums need the points per entry, and the plain sweep for d = 1.  The
+// weighted sums need the points per entry.  The
 // weights are read with broadcast vector loads (a lane-dependent zero in the
 // address), which leaves the scalar path to the offsets and the candidates'
 // tile records; the next group of 8 points (after a tile's last group, the
@@ -570,6 +576,7 @@ __device__ __forceinline__ SplitSum sweep_split_valu(const SweepIn& in, const Sw
                                                          int nsplit, double M, int J, unsigned long long cand) {
   constexpr bool CERT = MODE == kSweepCert;
   constexpr bool BARY = MODE == kSweepBary;
+  static_assert(CERT || BARY, "the plain sweep is sweep_split_mfma");
   const int lane0 = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
   SplitSum r{M, 0.0f, 0.0f, {0.0f, 0.0f, 0.0f}, J, 0};
   double Mth = M + kThresh;      // the exact-max gate, updated with M
@@ -678,7 +685,7 @@ __device__ __forceinline__ SplitSum sweep_split_valu(const SweepIn& in, const Sw
 template <int D, int MODE>
 __device__ __forceinline__ SplitSum sweep_split(const SweepIn& in, const SweepOut<D>& o, int split, int nsplit,
                                                 double M, int J, unsigned long long cand) {
-  if constexpr (MODE == kSweepPlain && D > 1) return sweep_split_mfma<D>(in, o, split, nsplit, M, J, cand);
+  if constexpr (MODE == kSweepPlain) return sweep_split_mfma<D>(in, o, split, nsplit, M, J, cand);
   else return sweep_split_valu<D, MODE>(in, o, split, nsplit, M, J, cand);
 }
 
@@ -701,7 +708,14 @@ struct RecOf { typedef PartialRec type; };
 template <>
 struct RecOf<kSweepCert> { typedef PartialCert type; };
 
-constexpr int kSweepWaves = 5;  // wavefronts per SIMD the sweeps' registers are held to
+// Wavefronts per SIMD that a sweep's registers are held to, as measured.  Plain:
+// d = 3 at 5 (6 spills, 4 is 5% slower), d = 1 and 2 at 6 (5 lets the compiler
+// interleave the quarters until it spills: 3% slower).  With costs or
+// coordinates at 4 (1 to 2% faster than 5 and 6).
+template <int D, int MODE>
+constexpr int sweep_waves() {
+  return MODE != kSweepPlain ? 4 : D == 3 ? 5 : 6;
+}
 
 // One block of kSweepBlock outputs (bx) against one split of the input tiles,
 // its records written to memory for k_finish.
@@ -761,7 +775,7 @@ __device__ __forceinline__ void sweep_block(const LaunchCtx& c, int nsplit, doub
 // The direction is a template parameter, as the dimension and the mode, so that
 // every argument sits at a fixed place and all of them are loaded at once.
 template <int D, int MODE, bool ROW>
-__global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSweepWaves))) void k_sweep(
+__global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(sweep_waves<D, MODE>()))) void k_sweep(
     LaunchCtx c, int nsplit, double eps, int own, int kofs) {
   // blockIdx.x is the split and blockIdx.y the output block:
   // consecutive workgroups go to consecutive XCDs, so the splits of one output
@@ -776,7 +790,7 @@ __global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSw
 // of a list over several problems; the arithmetic per item is the same as in
 // the single-problem launch.
 template <int D, int MODE, bool ROW>
-__global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(kSweepWaves))) void k_sweep_batch(
+__global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(sweep_waves<D, MODE>()))) void k_sweep_batch(
     const BatchItem* __restrict__ items, const LaunchCtx* __restrict__ descs, int kofs) {
   const BatchItem it = items[blockIdx.x];
   const LaunchCtx& c = descs[it.prob];

@@ -237,7 +237,7 @@ BDRS_API bdrs_status bdrs_set_hints(bdrs_solver s, const int32_t *row_hint, cons
  * out_j = LSE_i( w_i - C_ij / eps ) (the column update) when transpose != 0.
  * w and out are device float64 in original point order (length n / m resp.
  * m / n); the sweep itself runs in float32 on weights taken relative to
- * their tile maximum.  Uses the solver's workspace (clobbers its sweep buffers but not
+ * their tile's plane fit.  Uses the solver's workspace (clobbers its sweep buffers but not
  * the dual state).  Synchronises the stream. */
 BDRS_API bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps,
                      const double *w, double *out);

@@ -1276,22 +1276,15 @@ bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps, const double*
   const bool tr = transpose != 0;
   const int splits = tr ? s->L.splits_col : s->L.splits_row;
   hipError_t e;
-  if (!s->read_ev) HIPCHK(hipEventCreateWithFlags(&s->read_ev, hipEventDisableTiming));
   if ((e = launch_pack(c, tr, w, eps)) != hipSuccess) return hip_status(e, "pack");
-  HIPCHK(hipEventRecord(s->read_ev, c.stream));
-  e = sweep(s, tr, false, kFinishLse, splits, eps, out);
   s->packed_rows = false;
-  const bdrs_status st = e == hipSuccess ? repack(s) : BDRS_OK;
-  // on return w has been read and what was enqueued before has ended; the wait
-  // comes last, so that the launches do not wait for it (a wait with a copy of
-  // k before the sweep left the GPU idle for 10 us of 37)
-  const hipError_t ew = hipEventSynchronize(s->read_ev);
-  if (e != hipSuccess) return hip_status(e, "sweep");
-  if (ew != hipSuccess) {
-    s->packed_rows = false;  // nothing may have run (a stream under capture)
-    return hip_status(ew, "lse");
-  }
-  return st;
+  if ((e = sweep(s, tr, false, kFinishLse, splits, eps, out)) != hipSuccess) return hip_status(e, "sweep");
+  const bdrs_status st = repack(s);
+  if (st != BDRS_OK) return st;
+  // on return out is written; the one wait comes last, so that no launch waits
+  // for it (one with a copy of k before the sweep left the GPU idle for 10 us of 37)
+  HIPCHK(hipStreamSynchronize(c.stream));
+  return BDRS_OK;
 }
 
 bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col_marg, bdrs_plan_stats* out) {
@@ -1519,7 +1512,6 @@ bdrs_status bdrs_destroy(bdrs_solver s) {
   hipError_t e = hipStreamSynchronize(s->ctx.stream);
   // teardown: nothing to report
   for (hipEvent_t ev : s->ev_pool) (void)hipEventDestroy(ev);
-  if (s->read_ev) (void)hipEventDestroy(s->read_ev);
   if (s->blk_exec) (void)hipGraphExecDestroy(s->blk_exec);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   delete s;

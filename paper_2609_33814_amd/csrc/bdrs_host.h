@@ -133,7 +133,6 @@ struct bdrs_solver_ {
   bool packed_rows = false; // rows.A holds log alpha-hat of iteration k-1
   // sweep timing (bdrs_profile)
   bool prof = false;
-  hipEvent_t read_ev = nullptr;    // a call's input has been read (created on demand)
   std::vector<hipEvent_t> ev_pool;  // created on demand, reused after each read
   size_t ev_used = 0;
   double prof_entries = 0.0;

@@ -1276,6 +1276,12 @@ bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps, const double*
   const bool tr = transpose != 0;
   const int splits = tr ? s->L.splits_col : s->L.splits_row;
   hipError_t e;
+  // the call waits for its result, which a stream under capture refuses: asked
+  // before the first launch, so that nothing of the call stays in the capture
+  // (the default stream cannot be under capture)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (c.stream) HIPCHK(hipStreamIsCapturing(c.stream, &cap));
+  if (cap != hipStreamCaptureStatusNone) return hip_status(hipErrorStreamCaptureUnsupported, "lse");
   if ((e = launch_pack(c, tr, w, eps)) != hipSuccess) return hip_status(e, "pack");
   s->packed_rows = false;
   if ((e = sweep(s, tr, false, kFinishLse, splits, eps, out)) != hipSuccess) return hip_status(e, "sweep");

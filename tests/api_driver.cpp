@@ -4,7 +4,8 @@
 // line; prints "ok" at the end.
 //
 // The simulated stream counts its unfinished launches, so a call that returns
-// before its results are there is seen.
+// before its results are there is seen.  While it is under capture launches go
+// into the capture and a wait is refused.
 #include "bdrs_host.h"
 
 #include <cstdio>
@@ -17,7 +18,9 @@ using namespace bdrs;
 
 namespace {
 
-int g_pending = 0;  // launches and copies enqueued and not yet waited for
+int g_pending = 0;         // launches and copies enqueued and not yet waited for
+bool g_capturing = false;  // the stream is under capture
+int g_captured = 0;        // launches that went into the capture
 
 #define EXPECT(cond)                                                              \
   do {                                                                            \
@@ -28,7 +31,7 @@ int g_pending = 0;  // launches and copies enqueued and not yet waited for
   } while (0)
 
 hipError_t launched() {
-  ++g_pending;
+  ++(g_capturing ? g_captured : g_pending);
   return hipSuccess;
 }
 
@@ -55,7 +58,14 @@ hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
   std::memset(d, v, n);
   return ++g_pending, hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return g_pending = 0, hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+  if (g_capturing) return hipErrorStreamCaptureUnsupported;
+  return g_pending = 0, hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
+  *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipStreamCreateWithFlags(hipStream_t*, unsigned) { return hipErrorNotSupported; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
@@ -176,11 +186,24 @@ void results_are_there() {
   }
 }
 
+// A call that has to wait refuses a stream under capture and leaves nothing in it.
+void refused_under_capture() {
+  Problem p;
+  g_capturing = true;
+  for (int transpose = 0; transpose < 2; ++transpose) {
+    EXPECT(bdrs_lse(p.s, transpose, 0.1, p.w.data(), p.out.data()) == BDRS_E_DEVICE);
+    EXPECT(g_captured == 0);
+  }
+  g_capturing = false;
+  EXPECT(bdrs_lse(p.s, 0, 0.1, p.w.data(), p.out.data()) == BDRS_OK);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "results_are_there") results_are_there();
+  else if (name == "refused_under_capture") refused_under_capture();
   else return 2;
   std::printf("ok\n");
   return 0;

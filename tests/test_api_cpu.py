@@ -28,7 +28,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["results_are_there"])
+@pytest.mark.parametrize("scenario", ["results_are_there", "refused_under_capture"])
 def test_host_side(driver, scenario):
     res = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0 and res.stdout.strip().endswith("ok"), res.stdout + res.stderr

@@ -458,14 +458,24 @@ bdrs_status enqueue_iteration(bdrs_solver s, bool cert, int kofs) {
   return BDRS_OK;
 }
 
-// re-derives the packed sweep weights from the dual state (after bdrs_lse or a repair pass)
+// re-derives the packed sweep weights from the dual state
 bdrs_status repack(bdrs_solver s) {
   const LaunchCtx& c = s->ctx;
   const hipError_t e = launch_repack(c);
   if (e != hipSuccess) return hip_status(e, "repack");
+  s->weights_replaced = false;
   if (s->k > 0) s->packed_rows = true;
   return BDRS_OK;
 }
+
+// before a call packs other weights; repack ends it
+void replace_weights(bdrs_solver s) {
+  s->weights_replaced = true;
+  s->packed_rows = false;
+}
+
+// before a sweep of the state: what a call that failed has left is put right
+bdrs_status restore_weights(bdrs_solver s) { return s->weights_replaced ? repack(s) : BDRS_OK; }
 
 // certificate record (kCertSlots doubles, host) -> bdrs_cert, updating the best bounds
 // Copies the dual state and the hints into the retained-state region
@@ -559,7 +569,7 @@ bdrs_status read_cert(bdrs_solver s, bool repair, bdrs_cert* out) {
 // packed other weights or another temperature).
 bdrs_status enqueue_cert_only(bdrs_solver s) {
   bdrs_status st;
-  if ((!s->packed_rows || separate_cert(s)) && (st = repack(s)) != BDRS_OK) return st;
+  if ((!s->packed_rows || s->weights_replaced || separate_cert(s)) && (st = repack(s)) != BDRS_OK) return st;
   const double eps = eps_row_at(s, s->k - 1);
   hipError_t e;
   if ((e = sweep(s, true, true, kFinishCertOnly, s->L.splits_col, eps)) != hipSuccess)
@@ -571,11 +581,13 @@ bdrs_status enqueue_repair(bdrs_solver s) {
   const LaunchCtx& c = s->ctx;
   hipError_t e;
   const double eps = eps_row_at(s, s->k - 1);
+  s->weights_replaced = true;  // of the columns
   if ((e = launch_repair_pack(c)) != hipSuccess) return hip_status(e, "repair pack");
   if ((e = sweep(s, false, false, kFinishRepair, s->L.splits_row, eps)) != hipSuccess)
     return hip_status(e, "repair sweep");
   if ((e = launch_repair_reduce(c)) != hipSuccess) return hip_status(e, "repair reduce");
   if ((e = launch_prologue(c)) != hipSuccess) return hip_status(e, "prologue");  // restore cols.A
+  s->weights_replaced = false;
   return BDRS_OK;
 }
 
@@ -775,6 +787,7 @@ bdrs_status check_batch_call(const bdrs_solver* solvers, int32_t count, double t
 bdrs_status check_batch_members(const bdrs_solver* solvers, int32_t count, int32_t cert_every) {
   bdrs_status st;
   for (int i = 0; i < count; ++i) {
+    if ((st = restore_weights(solvers[i])) != BDRS_OK) return st;
     if ((st = sync_k(solvers[i])) != BDRS_OK) return st;
     if (solvers[i]->k % cert_every)
       return fail(BDRS_E_STATE, "solvers[%d] is at iteration %lld, not a multiple of cert_every", i, solvers[i]->k);
@@ -1079,6 +1092,8 @@ bdrs_status bdrs_step(bdrs_solver s, int32_t iters) {
   if (!s) return fail(BDRS_E_INVALID, "solver is NULL");
   if (iters < 0) return fail(BDRS_E_INVALID, "iters must be >= 0");
   if (iters == 0) return BDRS_OK;
+  const bdrs_status rst = restore_weights(s);
+  if (rst != BDRS_OK) return rst;
   for (int32_t i = 0; i < iters; ++i) {
     bdrs_status st = enqueue_iteration(s, false, i);
     if (st != BDRS_OK) return st;
@@ -1152,6 +1167,7 @@ bdrs_status bdrs_solve(bdrs_solver s, double tau, int32_t tau_relative, int32_t 
   bdrs_cert ce{};
   bool have = false;
   bdrs_status st0 = sync_k(s);
+  if (st0 == BDRS_OK) st0 = restore_weights(s);
   if (st0 != BDRS_OK) return st0;
   // the captured block needs the certificate fused into the last iteration
   // and no host-computed temperature (separate certificate sweep, repair)
@@ -1256,12 +1272,13 @@ bdrs_status bdrs_set_state(bdrs_solver s, const double* log_alpha, const double*
   s->U_best = INFINITY;
   s->L_best = -INFINITY;
   s->kU = s->kL = -1;
-  s->packed_rows = false;
+  replace_weights(s);  // the state's are other ones now
   bdrs_status st = BDRS_OK;
   if (log_alpha_hat) st = repack(s);
   else {
     hipError_t e2 = launch_prologue(c);
     if (e2 != hipSuccess) st = hip_status(e2, "prologue");
+    else s->weights_replaced = false;  // the next row update packs the rows
   }
   if (st != BDRS_OK) return st;
   HIPCHK(hipStreamSynchronize(c.stream));
@@ -1282,8 +1299,8 @@ bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps, const double*
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (c.stream) HIPCHK(hipStreamIsCapturing(c.stream, &cap));
   if (cap != hipStreamCaptureStatusNone) return hip_status(hipErrorStreamCaptureUnsupported, "lse");
+  replace_weights(s);
   if ((e = launch_pack(c, tr, w, eps)) != hipSuccess) return hip_status(e, "pack");
-  s->packed_rows = false;
   if ((e = sweep(s, tr, false, kFinishLse, splits, eps, out)) != hipSuccess) return hip_status(e, "sweep");
   const bdrs_status st = repack(s);
   if (st != BDRS_OK) return st;
@@ -1302,6 +1319,7 @@ bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col
   // X^k = diag(alpha^{k-1}) K^{.lambda k} diag(beta^{k-1}): kernel temperature eta / (lambda k)
   const double eps = s->prm.eta / (s->prm.lambda * (double)s->k);
   hipError_t e;
+  replace_weights(s);
   if ((e = launch_pack_state(c, false, eps)) != hipSuccess) return hip_status(e, "pack beta");
   if ((e = launch_sweep_bary(c, s->L.splits_row, eps)) != hipSuccess) return hip_status(e, "row sweep");
   if ((e = launch_finish(c, false, kFinishPlanRow, s->L.splits_row, bary, 0)) != hipSuccess)
@@ -1328,17 +1346,17 @@ bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col
     out->col_max_rel = h[5];
     out->mass = h[6];
   }
-  s->packed_rows = false;
   return repack(s);
 }
 
 // Two-sided rounding of the state plan X = diag(alpha) K diag(beta) at eps
 // (Altschuler, Weed and Rigollet 2017, Algorithm 2) in three sweeps: log x in
 // plan_row, log y in plan_col, e_r in plan_aux, e_c in mu, <C, G> and
-// ||e_r||_1 in plan_stats[8..11].  The rows are left packed with other weights.
+// ||e_r||_1 in plan_stats[8..11].  Both sides are left packed with other weights.
 bdrs_status enqueue_round(bdrs_solver s, double eps) {
   const LaunchCtx& c = s->ctx;
   hipError_t e;
+  replace_weights(s);
   // 1: row sums of X and x = min(1, r / X 1)
   if ((e = launch_pack_state(c, false, eps)) != hipSuccess) return hip_status(e, "pack beta");
   if ((e = sweep(s, false, false, kFinishRound1, s->L.splits_row, eps)) != hipSuccess)
@@ -1352,7 +1370,6 @@ bdrs_status enqueue_round(bdrs_solver s, double eps) {
   if ((e = sweep(s, false, true, kFinishRound3, s->L.splits_row, eps)) != hipSuccess)
     return hip_status(e, "cost sweep");
   if ((e = launch_round_reduce(c)) != hipSuccess) return hip_status(e, "reduce");
-  s->packed_rows = false;
   return BDRS_OK;
 }
 
@@ -1505,7 +1522,7 @@ bdrs_status bdrs_restore_best(bdrs_solver s, int64_t* iters_done) {
   long long k = s->best_k;
   HIPCHK(hipMemcpyAsync(&c.ctrl->k, &k, sizeof k, hipMemcpyHostToDevice, c.stream));
   s->k = k;
-  s->packed_rows = false;
+  replace_weights(s);
   const bdrs_status st = repack(s);
   if (st != BDRS_OK) return st;
   HIPCHK(hipStreamSynchronize(c.stream));

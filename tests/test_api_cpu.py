@@ -19,7 +19,7 @@ def driver(tmp_path_factory):
         pytest.skip("g++ or the HIP headers are not available")
     exe = str(tmp_path_factory.mktemp("api") / "api_driver")
     # what hipcc's own headers would define
-    hip = ["-D__HIP_PLATFORM_AMD__", "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=(&x)"]
+    hip = ["-D__HIP_PLATFORM_AMD__", "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=x"]
     cmd = [cxx, "-std=c++17", "-O1", *hip, "-I", CSRC, "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(ROCM, "include"), "-x", "c++", os.path.join(CSRC, "bdrs_api.hip"),
            os.path.join(ROOT, "tests", "api_driver.cpp"), "-o", exe]
@@ -28,7 +28,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["results_are_there", "refused_under_capture"])
+@pytest.mark.parametrize("scenario", ["results_are_there", "refused_under_capture", "weights_after_an_error",
+                                      "weights_after_a_numeric_error"])
 def test_host_side(driver, scenario):
     res = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0 and res.stdout.strip().endswith("ok"), res.stdout + res.stderr

@@ -265,6 +265,11 @@ struct SplitSum {
   int evaluated;  // input tiles this wavefront evaluated (the same on every lane)
 };
 
+// A value that is the same on every lane, held in a scalar register.
+__device__ __forceinline__ float uniform(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
 // own: the record of the outputs' own tile, whose box (widened against the
 // rounding of its centre and radius) holds the wavefront's 64 points.
 template <int D>
@@ -281,6 +286,15 @@ __device__ __forceinline__ SweepOut<D> sweep_out(const float (&P)[D], const Tile
     o.P[d] = P[d];
     o.blo[d] = ctr - half;
     o.bhi[d] = ctr + half;
+    // d = 1: in scalar registers, without which the batched sweep spills four
+    // vector registers (3-d sweeps spill with it, their scalar ones being full).
+    // 100 iterations of a batch on lines: four problems of 777 to 5100 points
+    // 2.91..3.12 -> 2.82..2.95 ms, three of 9000 to 30000 points 12.67..12.86 ->
+    // 12.82..13.03 ms; at 5 wavefronts per SIMD instead 2.89..2.97 and 13.10..13.17 ms
+    if (D == 1) {
+      o.blo[d] = uniform(o.blo[d]);
+      o.bhi[d] = uniform(o.bhi[d]);
+    }
   }
   return o;
 }
@@ -754,10 +768,11 @@ struct RecOf { typedef PartialRec type; };
 template <>
 struct RecOf<kSweepCert> { typedef PartialCert type; };
 
-// Wavefronts per SIMD that a sweep's registers are held to, as measured.  Plain:
-// d = 3 at 5 (6 spills, 4 is 5% slower), d = 1 and 2 at 6 (5 lets the compiler
-// interleave the quarters until it spills: 3% slower).  With costs or
-// coordinates at 4 (1 to 2% faster than 5 and 6).
+// Wavefronts per SIMD that a sweep's registers must leave room for (a minimum:
+// the compiler may need fewer registers), as measured.  Plain: d = 3 at 5 (at 6 it
+// spills, 4 is 5% slower), d = 1 and 2 at 6 (at 5 the compiler interleaves the
+// quarters, which spills for d = 2 and is 3% slower).  With costs or coordinates
+// at 4, where 5 to 7 come out (asking for 5 or 6 was 1 to 2% slower).
 template <int D, int MODE>
 constexpr int sweep_waves() {
   return MODE != kSweepPlain ? 4 : D == 3 ? 5 : 6;

@@ -34,10 +34,13 @@ CERT_EVERY = 50
 # Serving: requests above this many implicit entries per sweep (a 256x256 grid
 # problem has 4.3e9; the GPU is saturated well below that) run one at a time.
 BIG_WORK = 1e9
-CU, LANES, CLK = 256, 64, 2.4e9
-EXP_SLOTS = 1        # issue slots of one v_exp_f32: the colour sweep's counters show 6.80 VALU
-                     # instructions per entry (one of them the exp) issued at 98% of the
-                     # 64 lane-ops/CU/cycle ceiling, which a 2-slot exp would put above 100%
+CU, SIMDS, LANES, CLK = 256, 4, 64, 2.4e9
+# Cycles that the plain sweep's work for one entry of a wavefront takes of the
+# float32 pipe, which its VALU and matrix instructions share (probe kernels, four
+# wavefronts per SIMD): the exp2, the add into the sum, and one rank-one matrix
+# step per dimension and for the weight; the first step of a tile, common to its
+# four quarters, counts a quarter.
+EXP_CYCLES, ADD_CYCLES, STEP_CYCLES = 8.2, 2.5, 2.03
 
 
 # HBM traffic of one k_sweep<2,0> launch on the 128x128 grids (16 row and 16
@@ -78,11 +81,10 @@ def measured_traffic(splits):
 
 
 def sweep_peak_gentries(dim: int) -> float:
-    """FP32 exp/VALU roofline of one sweep entry, in Gentries/s: the fewest
-    VALU issue slots an entry can take in the tile-expanded form (d FMAs,
-    1 add of the weight, the exp2, 1 add into the sum) on 256 CUs x 64 lanes
-    x 2.4 GHz."""
-    return CU * LANES * CLK / (dim + 2 + EXP_SLOTS) / 1e9
+    """Bound of the plain sweep in evaluated Gentries/s: the float32 pipe of every
+    SIMD busy with nothing but the entries' own instructions."""
+    cycles = EXP_CYCLES + ADD_CYCLES + (dim + 1.25) * STEP_CYCLES
+    return CU * SIMDS * LANES * CLK / cycles / 1e9
 
 
 def _oracle_rows(task):
@@ -641,7 +643,7 @@ def main() -> int:
     per_sweep_ms = prof["ms"] / max(prof["sweeps"], 1)
     implicit_rate = prob.m * prob.n / (per_sweep_ms * 1e-3) / 1e9
     # the roofline counts the entries the sweeps evaluated: tiles whose bound
-    # puts every term below 2^-64 of the running maximum are skipped
+    # puts every term below 2^-T of the running maximum are skipped
     evaluated_frac = prof["evaluated"] / max(prof["entries"], 1.0)
     achieved = implicit_rate * evaluated_frac
     peak = sweep_peak_gentries(prob.dim)

@@ -272,7 +272,7 @@ __device__ __forceinline__ float uniform(float v) {
 
 // own: the record of the outputs' own tile, whose box (widened against the
 // rounding of its centre and radius) holds the wavefront's 64 points.
-template <int D>
+template <int D, bool BATCH>
 __device__ __forceinline__ SweepOut<D> sweep_out(const float (&P)[D], const TileVals<D>& own, double kap2,
                                                  double tskip) {
   SweepOut<D> o;
@@ -286,12 +286,13 @@ __device__ __forceinline__ SweepOut<D> sweep_out(const float (&P)[D], const Tile
     o.P[d] = P[d];
     o.blo[d] = ctr - half;
     o.bhi[d] = ctr + half;
-    // d = 1: in scalar registers, without which the batched sweep spills four
-    // vector registers (3-d sweeps spill with it, their scalar ones being full).
-    // 100 iterations of a batch on lines: four problems of 777 to 5100 points
-    // 2.91..3.12 -> 2.82..2.95 ms, three of 9000 to 30000 points 12.67..12.86 ->
-    // 12.82..13.03 ms; at 5 wavefronts per SIMD instead 2.89..2.97 and 13.10..13.17 ms
-    if (D == 1) {
+    // batches on lines: in scalar registers, without which the sweep spills four
+    // vector registers (a 3-d one spills with it, its scalar ones being full, and
+    // on lines a single problem, which does not spill, takes up to 1.4% longer).
+    // 100 iterations of four problems of 777 to 5100 points 3.01..3.08 -> 2.98..2.99
+    // ms, of three of 9000 to 30000 points 12.77..12.82 -> 12.90..13.00 ms (at 5
+    // wavefronts per SIMD instead, without spilling too, 13.10..13.17 ms)
+    if (D == 1 && BATCH) {
       o.blo[d] = uniform(o.blo[d]);
       o.bhi[d] = uniform(o.bhi[d]);
     }
@@ -429,7 +430,7 @@ __device__ __forceinline__ float tile_max(gfloat* __restrict__ offs, gfloat* __r
 // two kinds from different wavefronts takes the sum of their times).  Measured
 // cycles per wavefront instruction: fused multiply-add 4.2 (any form with three
 // register operands or a scalar one), exp2 8.2, add 2.5 (4 after an exp2),
-// rank-one step 2.03 per input.  So an entry takes 19.4 cycles here against
+// rank-one step 2.03 per input.  So an entry takes 19.3 cycles here against
 // 25.8 on the VALU for d = 3, 17.3 against 21.6 for d = 2, 15.3 against 17.4
 // for d = 1; and the tile data comes by one vector load per coordinate instead
 // of a chain of scalar ones.  With blocks of 32 x 32 (v_mfma_f32_32x32x1), whose
@@ -780,7 +781,7 @@ constexpr int sweep_waves() {
 
 // One block of kSweepBlock outputs (bx) against one split of the input tiles,
 // its records written to memory for k_finish.
-template <int D, int MODE, bool ROW>
+template <int D, int MODE, bool ROW, bool BATCH>
 __device__ __forceinline__ void sweep_block(const LaunchCtx& c, int nsplit, double eps, int own, int kofs, int bx,
                                             int split, unsigned* __restrict__ tile_count, int slot) {
   constexpr bool BARY = MODE == kSweepBary;
@@ -809,7 +810,7 @@ __device__ __forceinline__ void sweep_block(const LaunchCtx& c, int nsplit, doub
   const CtrlVals raw = load_ctrl(c.ctrl);
   __builtin_amdgcn_sched_barrier(0);  // all of it under way before the first wait
   const CtrlVals cv = with_eps(raw, eps, own != 0);
-  const SweepOut<D> o = sweep_out<D>(P, own_tile, kap2_of<ROW>(cv, kofs), (double)ins.tskip);
+  const SweepOut<D> o = sweep_out<D, BATCH>(P, own_tile, kap2_of<ROW>(cv, kofs), (double)ins.tskip);
   double M;
   int J;
   warm_start<D>(in, o, j_hint, M, J);
@@ -844,7 +845,7 @@ __global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(swe
   // and each XCD reads the input tiles of only part of the splits (its L2
   // holds just those)
   const int slot = (blockIdx.y * gridDim.x + blockIdx.x) * (kSweepBlock / kTile) + threadIdx.x / kTile;
-  sweep_block<D, MODE, ROW>(c, nsplit, eps, own, kofs, blockIdx.y, blockIdx.x, c.tile_count, slot);
+  sweep_block<D, MODE, ROW, false>(c, nsplit, eps, own, kofs, blockIdx.y, blockIdx.x, c.tile_count, slot);
 }
 
 // Batched sweep: block i runs work item i = (problem, block of outputs, split)
@@ -855,7 +856,7 @@ __global__ __launch_bounds__(kSweepBlock) __attribute__((amdgpu_waves_per_eu(swe
     const BatchItem* __restrict__ items, const LaunchCtx* __restrict__ descs, int kofs) {
   const BatchItem it = items[blockIdx.x];
   const LaunchCtx& c = descs[it.prob];
-  sweep_block<D, MODE, ROW>(c, ROW ? c.splits_row : c.splits_col, 0.0, 0, kofs, it.blk, it.split, nullptr, 0);
+  sweep_block<D, MODE, ROW, true>(c, ROW ? c.splits_row : c.splits_col, 0.0, 0, kofs, it.blk, it.split, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------

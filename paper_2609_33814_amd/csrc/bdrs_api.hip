@@ -474,8 +474,25 @@ void replace_weights(bdrs_solver s) {
   s->packed_rows = false;
 }
 
-// before a sweep of the state: what a call that failed has left is put right
-bdrs_status restore_weights(bdrs_solver s) { return s->weights_replaced ? repack(s) : BDRS_OK; }
+// In a call that packs other weights: they are restored when it returns early, too
+// (what follows may be a replayed graph of iterations, which knows of no flag).
+struct RestoreOnReturn {
+  bdrs_solver s;
+  ~RestoreOnReturn() {
+    if (s->weights_replaced && launch_repack(s->ctx) == hipSuccess) s->weights_replaced = false;
+  }
+};
+
+// Before a sweep of the state: what a call that failed has left, its own
+// restoring included, is put right.  Into a capture it has not run yet.
+bdrs_status restore_weights(bdrs_solver s) {
+  if (!s->weights_replaced) return BDRS_OK;
+  const bdrs_status st = repack(s);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (s->ctx.stream) HIPCHK(hipStreamIsCapturing(s->ctx.stream, &cap));
+  if (cap != hipStreamCaptureStatusNone) s->weights_replaced = true;
+  return st;
+}
 
 // certificate record (kCertSlots doubles, host) -> bdrs_cert, updating the best bounds
 // Copies the dual state and the hints into the retained-state region
@@ -1110,6 +1127,7 @@ bdrs_status bdrs_certificate(bdrs_solver s, bdrs_cert* out) {
   bdrs_status st = sync_k(s);
   if (st != BDRS_OK) return st;
   if (s->k < 1) return fail(BDRS_E_STATE, "no iteration has run yet");
+  const RestoreOnReturn restore{s};
   if ((st = enqueue_cert_only(s)) != BDRS_OK) return st;
   const LaunchCtx& c = s->ctx;
   hipError_t e;
@@ -1169,6 +1187,7 @@ bdrs_status bdrs_solve(bdrs_solver s, double tau, int32_t tau_relative, int32_t 
   bdrs_status st0 = sync_k(s);
   if (st0 == BDRS_OK) st0 = restore_weights(s);
   if (st0 != BDRS_OK) return st0;
+  const RestoreOnReturn restore{s};  // a repair packs other weights
   // the captured block needs the certificate fused into the last iteration
   // and no host-computed temperature (separate certificate sweep, repair)
   const bool graphs = !repair && !separate_cert(s) && !(s->prm.flags & BDRS_F_NO_GRAPH) && !s->prof;
@@ -1299,6 +1318,7 @@ bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps, const double*
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (c.stream) HIPCHK(hipStreamIsCapturing(c.stream, &cap));
   if (cap != hipStreamCaptureStatusNone) return hip_status(hipErrorStreamCaptureUnsupported, "lse");
+  const RestoreOnReturn restore{s};
   replace_weights(s);
   if ((e = launch_pack(c, tr, w, eps)) != hipSuccess) return hip_status(e, "pack");
   if ((e = sweep(s, tr, false, kFinishLse, splits, eps, out)) != hipSuccess) return hip_status(e, "sweep");
@@ -1319,6 +1339,7 @@ bdrs_status bdrs_plan(bdrs_solver s, double* bary, double* row_marg, double* col
   // X^k = diag(alpha^{k-1}) K^{.lambda k} diag(beta^{k-1}): kernel temperature eta / (lambda k)
   const double eps = s->prm.eta / (s->prm.lambda * (double)s->k);
   hipError_t e;
+  const RestoreOnReturn restore{s};
   replace_weights(s);
   if ((e = launch_pack_state(c, false, eps)) != hipSuccess) return hip_status(e, "pack beta");
   if ((e = launch_sweep_bary(c, s->L.splits_row, eps)) != hipSuccess) return hip_status(e, "row sweep");
@@ -1380,6 +1401,7 @@ bdrs_status bdrs_round(bdrs_solver s, bdrs_round_stats* out) {
   if (st != BDRS_OK) return st;
   if (s->k < 1) return fail(BDRS_E_STATE, "rounding needs at least one finished iteration");
   const double eps = s->prm.eta / (s->prm.lambda * (double)s->k);  // the state plan's kernel
+  const RestoreOnReturn restore{s};
   if ((st = enqueue_round(s, eps)) != BDRS_OK) return st;
   const LaunchCtx& c = s->ctx;
   double h[4];
@@ -1402,6 +1424,7 @@ bdrs_status bdrs_export_plan(bdrs_solver s, int32_t kind, double* log_u, double*
   if (st != BDRS_OK) return st;
   if (s->k < 1) return fail(BDRS_E_STATE, "a plan needs at least one finished iteration");
   const LaunchCtx& c = s->ctx;
+  const RestoreOnReturn restore{s};
   hipError_t e;
   double h[kCertSlots];
   bdrs_plan_export info{};

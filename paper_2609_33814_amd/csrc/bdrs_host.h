@@ -131,8 +131,8 @@ struct bdrs_solver_ {
   double U_best = INFINITY, L_best = -INFINITY;
   long long kU = -1, kL = -1;
   bool packed_rows = false; // rows.A holds log alpha-hat of iteration k-1
-  // a call has packed other weights than the state's and not restored them (an
-  // error ended it early): whatever sweeps the state next restores them first
+  // a call has packed other weights than the state's and could not restore them:
+  // whatever sweeps the state next restores them first
   bool weights_replaced = false;
   // sweep timing (bdrs_profile)
   bool prof = false;

@@ -25,6 +25,7 @@ int g_pending = 0;         // launches and copies enqueued and not yet waited fo
 bool g_capturing = false;  // the stream is under capture
 int g_captured = 0;        // launches that went into the capture
 int g_fail_at = 0;         // the call into the runtime that fails (counted down; 0: none)
+bool g_fail_on = false;    // ... and all after it
 double g_round_cost = 1.0; // what the rounding's reduction gives
 // whose weights the sides hold, and sweeps of the state that read others
 bool g_rows_state = false, g_cols_state = false;
@@ -38,7 +39,11 @@ int g_wrong = 0;
     }                                                                             \
   } while (0)
 
-bool fails() { return g_fail_at > 0 && --g_fail_at == 0; }
+bool fails() {
+  if (g_fail_at == 0 || --g_fail_at > 0) return false;
+  if (g_fail_on) g_fail_at = 1;
+  return true;
+}
 
 hipError_t launched() {
   if (fails()) return hipErrorUnknown;
@@ -46,11 +51,11 @@ hipError_t launched() {
   return hipSuccess;
 }
 
-// f is what the launch does if it does not fail
+// f is what the launch does if it does not fail (into a capture: nothing yet)
 template <typename F>
 hipError_t launched(F f) {
   const hipError_t e = launched();
-  if (e == hipSuccess) f();
+  if (e == hipSuccess && !g_capturing) f();
   return e;
 }
 
@@ -286,18 +291,24 @@ bdrs_status use(Problem& p, int call) {
 }
 
 // A call that replaces the packed weights and ends early, wherever it does,
-// leaves a solver whose next call sweeps the state's weights.
+// leaves a solver whose next call sweeps the state's weights; if only one call
+// into the runtime failed, the state's weights are there when it returns (a graph
+// of iterations may be replayed next).
 void weights_after_an_error() {
+  for (int on = 0; on < 2; ++on)
   for (int call = 0; call < 7; ++call)
     for (int how = 0; how < 4; ++how) {
       const unsigned flags = call == 6 && how < 3 ? BDRS_F_REPAIR : 0;  // (not supported in batches)
       for (int n = 1;; ++n) {
         Problem p(flags);
         g_fail_at = n;
+        g_fail_on = on != 0;
         const bdrs_status st = use(p, call);
-        const bool failed = g_fail_at == 0;
+        const bool failed = st != BDRS_OK;
         g_fail_at = 0;
+        g_fail_on = false;
         EXPECT(st == (failed ? BDRS_E_DEVICE : BDRS_OK));
+        EXPECT(on || (g_rows_state && g_cols_state));
         const bdrs_status next = follow(p, how);
         EXPECT(next == BDRS_OK || next == BDRS_NOT_CONVERGED);
         EXPECT(g_wrong == 0);
@@ -313,10 +324,27 @@ void weights_after_a_numeric_error() {
     g_round_cost = NAN;
     EXPECT(use(p, 3) == BDRS_E_NUMERIC);
     g_round_cost = 1.0;
+    EXPECT(g_rows_state && g_cols_state);
     const bdrs_status next = follow(p, how);
     EXPECT(next == BDRS_OK || next == BDRS_NOT_CONVERGED);
     EXPECT(g_wrong == 0);
   }
+}
+
+// Weights restored inside a capture are not restored until it is replayed.
+void weights_after_a_capture() {
+  Problem p;
+  g_fail_at = 4;  // the sweep's epilogue and what follows it
+  g_fail_on = true;
+  EXPECT(use(p, 0) == BDRS_E_DEVICE);
+  g_fail_at = 0;
+  g_fail_on = false;
+  EXPECT(!g_cols_state);
+  g_capturing = true;
+  EXPECT(bdrs_step(p.s, 1) == BDRS_OK && g_captured > 0);
+  g_capturing = false;
+  EXPECT(bdrs_step(p.s, 1) == BDRS_OK);
+  EXPECT(g_wrong == 0);
 }
 
 }  // namespace
@@ -327,6 +355,7 @@ int main(int argc, char** argv) {
   else if (name == "refused_under_capture") refused_under_capture();
   else if (name == "weights_after_an_error") weights_after_an_error();
   else if (name == "weights_after_a_numeric_error") weights_after_a_numeric_error();
+  else if (name == "weights_after_a_capture") weights_after_a_capture();
   else return 2;
   std::printf("ok\n");
   return 0;

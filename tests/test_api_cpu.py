@@ -29,7 +29,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["results_are_there", "refused_under_capture", "weights_after_an_error",
-                                      "weights_after_a_numeric_error"])
+                                      "weights_after_a_numeric_error", "weights_after_a_capture"])
 def test_host_side(driver, scenario):
     res = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0 and res.stdout.strip().endswith("ok"), res.stdout + res.stderr

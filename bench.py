@@ -50,15 +50,15 @@ EXP_CYCLES, ADD_CYCLES, STEP_CYCLES = 8.2, 2.5, 2.03
 # device copy (x2.000 and x1.000).  It holds for the kernel sources with this
 # sha256 (of bdrs_kernels.hip followed by bdrs_internal.h) and those split
 # counts only; otherwise it is reported as null.
-TRAFFIC_KERNEL_SHA256 = "633d46953d215f376c287b60b5ff776a06218199df7e69343cad1dca31ba95eb"
+TRAFFIC_KERNEL_SHA256 = "6e74df697ee38949b8ce5749a9031ddbaa0a4eb115c80b6c8cb70db50a248bd7"
 TRAFFIC_SPLITS = (16, 16)
-TRAFFIC_BYTES_PER_LAUNCH = 6.41e6
+TRAFFIC_BYTES_PER_LAUNCH = 6.60e6
 # Counters of the same profile (per dispatch of k_sweep<2,0> in the replay):
-# VALU lane instructions and v_exp_f32 per evaluated entry (x 64 / evaluated
-# entries), VALU issue utilisation (lane instructions / duration / (256 x 64 x
-# 2.4 GHz)) and rocprof's VALUBusy.
-PROFILE_COUNTERS = {"valu_instr_per_evaluated_entry": 10.98, "exp_per_evaluated_entry": 1.023,
-                    "valu_issue_frac": 0.426, "VALUBusy": 26.3,
+# lane instructions (VALU and matrix) and v_exp_f32 per evaluated entry (x 64 /
+# evaluated entries), rank-one matrix steps per evaluated tile, issue utilisation
+# (lane instructions / duration / (256 x 64 x 2.4 GHz)) and rocprof's VALUBusy.
+PROFILE_COUNTERS = {"valu_instr_per_evaluated_entry": 5.58, "exp_per_evaluated_entry": 1.011,
+                    "matrix_steps_per_evaluated_tile": 13.0, "valu_issue_frac": 0.263, "VALUBusy": 15.3,
                     "source": "profiles/k_sweep_grid128x128.md"}
 
 

@@ -238,7 +238,8 @@ BDRS_API bdrs_status bdrs_set_hints(bdrs_solver s, const int32_t *row_hint, cons
  * w and out are device float64 in original point order (length n / m resp.
  * m / n); the sweep itself runs in float32 on weights taken relative to
  * their tile's plane fit.  Uses the solver's workspace (clobbers its sweep buffers but not
- * the dual state).  Synchronises the stream. */
+ * the dual state).  Synchronises the stream; one under capture is refused
+ * (BDRS_E_DEVICE) before anything is launched. */
 BDRS_API bdrs_status bdrs_lse(bdrs_solver s, int32_t transpose, double eps,
                      const double *w, double *out);
 

@@ -8,8 +8,9 @@ namespace bdrs {
 constexpr int kTile = 64;         // points per tile = one wavefront
 constexpr int kBlock = 256;       // threads per block of the O(n) kernels
 
-// threads per sweep block: the waves of one block share the input tiles of
-// their split (read once through the scalar cache for all of them)
+// threads per sweep block: the waves of one block walk the input tiles of one
+// split (the plain sweep loads their points by vector loads, one per lane and
+// coordinate; the sweeps with costs or coordinates through the scalar cache)
 #ifndef BDRS_SWEEP_BLOCK
 #define BDRS_SWEEP_BLOCK 256
 #endif

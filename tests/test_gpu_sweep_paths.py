@@ -1,7 +1,7 @@
 """The plain sweep (exponents on the matrix cores) and the certificate's sweep
 (exponents on the VALU) form the same sums, so an iteration's state must not
 depend on which of them ran: bit for bit, at the edges of the 64 x 64 tiles
-(partial halves of 32 inputs, one point into the next tile or output block),
+(partial quarters of 16 inputs, one point into the next tile or output block),
 for every dimension, at high and low temperature and with overrelaxation."""
 import numpy as np
 import pytest
